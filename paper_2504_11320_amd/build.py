@@ -14,9 +14,9 @@ from concurrent.futures import ThreadPoolExecutor
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
-SRC_NAMES = ("wait_sim_host.hip", "sim_known_wait.hip", "sim_known_fcfs.hip",
-             "sim_nested.hip", "sim_known_wait_tv.hip", "sim_known_fcfs_tv.hip",
-             "sim_nested_tv.hip", "sim_fcfs_dist.hip", "sim_wait_many.hip")
+SRC_NAMES = ("wait_sim_host.hip", "sim_wait.hip", "sim_known_fcfs.hip",
+             "sim_nested.hip", "sim_wait_tv.hip", "sim_known_fcfs_tv.hip",
+             "sim_nested_tv.hip", "sim_fcfs_dist.hip")
 SRCS = [os.path.join(CSRC, f) for f in SRC_NAMES]
 INC = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libwait_sim.so")
@@ -35,9 +35,8 @@ HIPCC_FLAGS = [
 # scheduler), as measured: the known-length WAIT and the Nested WAIT kernels
 # gain from the ILP-maximising one, the FCFS kernels lose.
 SCHED_FLAGS = {
-    "sim_known_wait.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"],
-    "sim_known_wait_tv.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"],
-    "sim_wait_many.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"],
+    "sim_wait.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"],
+    "sim_wait_tv.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"],
     "sim_nested.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"],
     "sim_nested_tv.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"],
 }

@@ -97,7 +97,9 @@ struct KArgs {
   int32_t any_tv;      // some job of this launch has time-varying rates
   int32_t lanes;       // replicas per wavefront (lanes >= this are padding)
   int32_t unit_n;      // WAIT launch whose jobs all have thresholds n_j = 1
-  int32_t any_caps;    // some Nested WAIT job of this launch has per-stage caps
+  int32_t any_caps;    // some job of this launch has per-stage caps
+  int32_t nr;          // WAIT: replicas per wavefront (a divisor of `lanes`)
+  int32_t min_waves;   // WAIT: wavefronts a launch is spread over, if it can be
   uint8_t *btrace;     // per-batch trace [R][btrace_cap] records, or null
   int64_t btrace_cap;
 };
@@ -422,16 +424,30 @@ __device__ __forceinline__ HistIdx hist_index_build(const double *E, int n, uint
   return H;
 }
 
-__device__ __forceinline__ int hist_bin_idx(const double *E, const uint8_t *T, const HistIdx &H,
-                                            double lat) {
-  const int64_t key = (int64_t)(dbits(lat) >> H.shift) - H.kmin;
-  const int kc = key < 0 ? 0 : (key >= H.K ? H.K - 1 : (int)key);
-  int pos = T[kc];
+// The bins of N latencies at once: their table reads and comparisons are
+// independent chains of LDS reads.
+template <int N>
+__device__ __forceinline__ void hist_bins(const double *E, const uint8_t *T, const HistIdx &H,
+                                          const double (&lat)[N], int (&pos)[N]) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const int64_t key = (int64_t)(dbits(lat[i]) >> H.shift) - H.kmin;
+    pos[i] = T[key < 0 ? 0 : (key >= H.K ? H.K - 1 : (int)key)];
+  }
   // a few steps at most (the table lands within H.steps edges): a copy of
   // the loop unrolled for run-time trip counts only adds branches and code
 #pragma unroll 1
-  for (int s = 0; s < H.steps; ++s) pos += E[pos] <= lat ? 1 : 0;
-  return pos;
+  for (int s = 0; s < H.steps; ++s) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) pos[i] += E[pos[i]] <= lat[i] ? 1 : 0;
+  }
+}
+__device__ __forceinline__ int hist_bin_idx(const double *E, const uint8_t *T, const HistIdx &H,
+                                            double lat) {
+  const double l1[1] = {lat};
+  int pos[1];
+  hist_bins<1>(E, T, H, l1, pos);
+  return pos[0];
 }
 
 // ------------------------------------------------------------- records --
@@ -546,13 +562,12 @@ __host__ __device__ constexpr int nested_group_width(int max_m, int max_seg) {
 }
 
 // Launchers, one per kernel family (defined next to their kernels).
-hipError_t launch_known_wait(int max_m, const KArgs &A, hipStream_t s);
+hipError_t launch_wait(int max_m, const KArgs &A, hipStream_t s);
 hipError_t launch_known_fcfs(int max_m, const KArgs &A, hipStream_t s);
 hipError_t launch_nested(int max_m, int max_seg, const KArgs &A, hipStream_t s);
 hipError_t launch_fcfs_dist(int max_m, const KArgs &A, hipStream_t s);
-hipError_t launch_wait_many(int max_m, const KArgs &A, hipStream_t s);
 // the kernels for launches with time-varying rates or an arrival list
-hipError_t launch_known_wait_tv(int max_m, const KArgs &A, hipStream_t s);
+hipError_t launch_wait_tv(int max_m, const KArgs &A, hipStream_t s);
 hipError_t launch_known_fcfs_tv(int max_m, const KArgs &A, hipStream_t s);
 hipError_t launch_nested_tv(int max_m, int max_seg, const KArgs &A, hipStream_t s);
 

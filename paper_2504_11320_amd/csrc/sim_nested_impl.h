@@ -51,7 +51,7 @@
 // from reordering them.
 #pragma once
 
-#include "sim_common.h"
+#include "sim_lanes.h"
 
 namespace wsim {
 namespace {
@@ -96,118 +96,6 @@ __device__ __forceinline__ NRec load_nrec(const NRec *p) {
 // charges a record implies need no table lookup: (l << 8) | type.
 __device__ __forceinline__ int32_t type_word(int32_t l, int32_t j) { return (l << 8) | j; }
 __device__ __forceinline__ int32_t plen(int32_t jw) { return jw >> 8; }
-
-// ---------------------------------------------------------- group lanes --
-// DPP lane permutations inside 16-lane rows (gfx9 encodings): swap neighbours
-// (quad_perm [1,0,3,2]), swap pairs (quad_perm [2,3,0,1]), mirror each half
-// row (lane i <-> 7-i), mirror the row (i <-> 15-i).  After the first two a
-// lane holds its quad's reduction; the half-row mirror pairs each lane with
-// one of the other quad of its 8, the row mirror with one of the other 8 of
-// its 16: an all-reduce over groups of 4, 8 or 16 aligned lanes that reads
-// no lane outside the group.
-constexpr int kDppSwap1 = 0xB1;
-constexpr int kDppSwap2 = 0x4E;
-constexpr int kDppHalfMirror = 0x141;
-constexpr int kDppMirror = 0x140;
-
-template <int CTRL>
-__device__ __forceinline__ uint32_t dpp32(uint32_t v) {
-  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, false);
-}
-template <int CTRL>
-__device__ __forceinline__ uint64_t dpp64(uint64_t v) {
-  return ((uint64_t)dpp32<CTRL>((uint32_t)(v >> 32)) << 32) | dpp32<CTRL>((uint32_t)v);
-}
-
-// Shift by one lane inside the 16-lane rows: row_shl:1 (lane i takes lane
-// i+1) and row_shr:1 (lane i takes lane i-1); a row's end lane keeps 0.
-constexpr int kDppShl1 = 0x101;
-constexpr int kDppShr1 = 0x111;
-
-// Groups of 32 or 64 lanes combine the 16-lane rows with lane-index XOR
-// exchanges (16, then 32).
-template <int MASK>
-__device__ __forceinline__ uint32_t xor32(uint32_t v) {
-  return (uint32_t)__shfl_xor((int)v, MASK, 64);
-}
-template <int MASK>
-__device__ __forceinline__ uint64_t xor64(uint64_t v) {
-  return ((uint64_t)xor32<MASK>((uint32_t)(v >> 32)) << 32) | xor32<MASK>((uint32_t)v);
-}
-
-template <int G, typename Op>
-__device__ __forceinline__ uint64_t group_reduce64(uint64_t v, Op op) {
-  v = op(v, dpp64<kDppSwap1>(v));
-  v = op(v, dpp64<kDppSwap2>(v));
-  if constexpr (G >= 8) v = op(v, dpp64<kDppHalfMirror>(v));
-  if constexpr (G >= 16) v = op(v, dpp64<kDppMirror>(v));
-  if constexpr (G >= 32) v = op(v, xor64<16>(v));
-  if constexpr (G >= 64) v = op(v, xor64<32>(v));
-  return v;
-}
-template <int G>
-__device__ __forceinline__ int64_t group_sum(int64_t v) {
-  return (int64_t)group_reduce64<G>((uint64_t)v, [](uint64_t a, uint64_t b) { return a + b; });
-}
-template <int G, typename Op>
-__device__ __forceinline__ uint32_t group_reduce32(uint32_t v, Op op) {
-  v = op(v, dpp32<kDppSwap1>(v));
-  v = op(v, dpp32<kDppSwap2>(v));
-  if constexpr (G >= 8) v = op(v, dpp32<kDppHalfMirror>(v));
-  if constexpr (G >= 16) v = op(v, dpp32<kDppMirror>(v));
-  if constexpr (G >= 32) v = op(v, xor32<16>(v));
-  if constexpr (G >= 64) v = op(v, xor32<32>(v));
-  return v;
-}
-// Sum of values whose group total fits in 32 bits (per-batch memory changes
-// and counts).
-template <int G>
-__device__ __forceinline__ int32_t group_sum32(int32_t v) {
-  return (int32_t)group_reduce32<G>((uint32_t)v, [](uint32_t a, uint32_t b) { return a + b; });
-}
-template <int G>
-__device__ __forceinline__ uint32_t group_or(uint32_t v) {
-  return group_reduce32<G>(v, [](uint32_t a, uint32_t b) { return a | b; });
-}
-template <int G>
-__device__ __forceinline__ double group_min(double v) {
-  const uint64_t r = group_reduce64<G>((uint64_t)__double_as_longlong(v), [](uint64_t a, uint64_t b) {
-    const double x = __longlong_as_double((long long)a), y = __longlong_as_double((long long)b);
-    return y < x ? b : a;
-  });
-  return __longlong_as_double((long long)r);
-}
-// The value of segment lane k+1 (seg_next) or k-1 (seg_prev) of the group;
-// the group's end lanes get values they do not use.
-template <int G>
-__device__ __forceinline__ uint32_t seg_next(uint32_t v) {
-  if constexpr (G <= 16)
-    return dpp32<kDppShl1>(v);
-  else
-    return (uint32_t)__shfl_down((int)v, 1u, G);
-}
-template <int G>
-__device__ __forceinline__ uint32_t seg_prev(uint32_t v) {
-  if constexpr (G <= 16)
-    return dpp32<kDppShr1>(v);
-  else
-    return (uint32_t)__shfl_up((int)v, 1u, G);
-}
-template <int G>
-__device__ __forceinline__ uint64_t seg_prev64(uint64_t v) {
-  return ((uint64_t)seg_prev<G>((uint32_t)(v >> 32)) << 32) | seg_prev<G>((uint32_t)v);
-}
-
-// The group's G bits of a wavefront ballot (bit g = group lane g).
-template <int G>
-__device__ __forceinline__ uint64_t group_bits(bool pred) {
-  const uint64_t b = __ballot(pred);
-  if constexpr (G == 64) {
-    return b;
-  } else {
-    return (b >> (threadIdx.x & (64 - G))) & ((1ull << G) - 1ull);
-  }
-}
 
 // Wait for every outstanding memory operation of the wavefront; also a
 // compiler barrier for memory accesses.
@@ -801,14 +689,14 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) si
   for (int64_t it = 0; it < A.horizon && !stopped; ++it) {
     // ---- refill the draw rings, all active lanes together -----------------
     if (!trace) {
-      const uint64_t act = __ballot(1);
+      const uint64_t act = ballot(1);
       const int nact = __popcll(act);
       const int wrank = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(act >> 32),
                                                       __builtin_amdgcn_mbcnt_lo((uint32_t)act, 0u));
       const uint32_t avail = gend - kj - 1u;
-      if (__ballot(is_t && avail < kLow) != 0) {
+      if (ballot(is_t && avail < kLow) != 0) {
         const bool room = is_t && avail <= (uint32_t)(GR - GU);
-        const uint64_t need = __ballot(room);
+        const uint64_t need = ballot(room);
         if (room) {
           const int rq = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(need >> 32),
                                                         __builtin_amdgcn_mbcnt_lo((uint32_t)need, 0u));

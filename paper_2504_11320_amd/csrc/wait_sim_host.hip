@@ -251,6 +251,7 @@ int guarded(F &&body) noexcept {
 #endif
 constexpr int64_t kTargetWaves = WS_TARGET_WAVES;
 constexpr int64_t kTargetWavesNested = 2 * WS_TARGET_WAVES;
+constexpr int32_t kMinWavesWait = 2048;
 
 int ceil_log2(uint64_t x) {
   int k = 0;
@@ -879,6 +880,7 @@ int advance_impl(const ws_job *jobs, int32_t n_jobs, const Layout &Lo, int64_t h
     B.off_list = Lo.list_off[pk];
     B.n_list = Lo.list_count[pk];
     B.lanes = Lo.lanes[pk];
+    B.min_waves = kMinWavesWait;
     B.any_trace = B.any_tv = B.any_caps = 0;
     B.unit_n = pk == WS_WAIT ? 1 : 0;
     for (int i = 0; i < n_jobs; ++i) {
@@ -897,7 +899,7 @@ int advance_impl(const ws_job *jobs, int32_t n_jobs, const Layout &Lo, int64_t h
     else if (pk == kFcfsDist)
       e = launch_fcfs_dist(Lo.max_m[pk], B, ls);
     else
-      e = pk == WS_WAIT ? launch_known_wait(Lo.max_m[pk], B, ls)
+      e = pk == WS_WAIT ? launch_wait(Lo.max_m[pk], B, ls)
                         : launch_known_fcfs(Lo.max_m[pk], B, ls);
     if (e != hipSuccess) return fail(WS_EDEVICE, std::string("launch: ") + hipGetErrorString(e));
     launched++;
