@@ -48,17 +48,18 @@ CSRC = os.path.join(ROOT, "paper_2504_11320_amd", "csrc")
 # Per workload: the committed rocprofv3 HBM counter summary of its dominant
 # kernel and the sources that define that kernel (hashed to tie the summary
 # to the kernel it was measured on).
-_WAIT_SRCS = ("sim_wait_impl.h", "sim_lanes.h", "sim_wait.hip", "sim_common.h")
+_WAIT_SRCS = ("sim_wait_impl.h", "sim_arrivals.h", "sim_lanes.h", "sim_wait.hip", "sim_common.h")
 PROFILES = {
     "wait-llama": ("sim_known_wait_3type_32x1024x1e5", _WAIT_SRCS),
     "wait-cyclic": ("sim_known_wait_tv_3type_cyclic_32x1024x1e5",
-                    ("sim_wait_impl.h", "sim_lanes.h", "sim_wait_tv.hip", "sim_common.h")),
+                    ("sim_wait_impl.h", "sim_arrivals.h", "sim_lanes.h", "sim_wait_tv.hip",
+                     "sim_common.h")),
     "nested-geometric": ("sim_nested_3type_geometric_32x1024x1e5",
                          ("sim_nested_impl.h", "sim_lanes.h", "sim_nested.hip", "sim_common.h")),
     "nested-heavytail": ("sim_nested_10type_lognormal_8192x1e6",
                          ("sim_nested_impl.h", "sim_lanes.h", "sim_nested.hip", "sim_common.h")),
     "fcfs-chunked": ("sim_known_fcfs_3type_chunk512_32x1024x1e5",
-                     ("sim_known_impl.h", "sim_known_fcfs.hip", "sim_common.h")),
+                     ("sim_fcfs_impl.h", "sim_arrivals.h", "sim_lanes.h", "sim_fcfs.hip", "sim_common.h")),
 }
 
 
@@ -386,7 +387,7 @@ def main() -> int:
                 "launches": args.steps,
                 "kernel": (f"sim_nested_kernel ({m} types)" if policy == "nested"
                            else f"sim_wait_kernel ({m} types)" if policy.startswith("wait")
-                           else f"sim_known_kernel ({policy}, {m} types)")
+                           else f"sim_fcfs_kernel ({m} types)")
                           + (f", time-varying rates ({rate_pts} points, "
                              f"{cpa:.3f} candidates per arrival)" if rate_pts else "")}
 

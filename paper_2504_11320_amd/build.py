@@ -14,8 +14,8 @@ from concurrent.futures import ThreadPoolExecutor
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
-SRC_NAMES = ("wait_sim_host.hip", "sim_wait.hip", "sim_known_fcfs.hip",
-             "sim_nested.hip", "sim_wait_tv.hip", "sim_known_fcfs_tv.hip",
+SRC_NAMES = ("wait_sim_host.hip", "sim_wait.hip", "sim_fcfs.hip",
+             "sim_nested.hip", "sim_wait_tv.hip", "sim_fcfs_tv.hip",
              "sim_nested_tv.hip", "sim_fcfs_dist.hip")
 SRCS = [os.path.join(CSRC, f) for f in SRC_NAMES]
 INC = os.path.join(ROOT, "include")

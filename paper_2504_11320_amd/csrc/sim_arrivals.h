@@ -1,0 +1,197 @@
+// sim_arrivals.h -- the arrival processes of a replica on a group of G lanes,
+// one request type per lane: Poisson at a constant rate, or thinned with a rate
+// profile.  An arrival process does not depend on what the simulation does, so
+// the whole wavefront draws arrival times ahead of use into a ring per lane.
+#pragma once
+
+#include "sim_lanes.h"
+
+namespace wsim {
+namespace {
+
+// TV: rate profiles are supported.  RING: ring entries of a wavefront.
+template <int G, bool TV, int RING>
+struct Arrivals {
+  static constexpr int NP = TV ? kMaxRatePts : 1;
+  struct Lds {
+    double at[RING];
+    uint32_t ak[TV ? RING : 1];  // acceptance words, then candidate indices
+    RateProfLds<TV ? G : 1, NP> prof;
+    uint8_t req[64];
+  };
+  Lds &S;
+  int tx, gl, act_log2, gu_log2, P;
+  uint32_t dm, gu;  // ring depth - 1; draws added per request
+  uint64_t seed;
+  uint32_t rid;
+  double lam;
+  bool tv;
+  Mask draw_m;  // lanes that draw
+  // The pending arrival (tn) and the next (tn2) lead the ring of entries rp ..
+  // re-1, whose last is at te; kc is the next candidate to draw, tl the clock
+  // it starts from.
+  double tn = INFINITY, tn2 = INFINITY, te = INFINITY, tl = 0.0;
+  uint32_t rp = 0, re = 0, kc = 0;
+  bool ended = false;     // (TV) no further arrivals
+  bool thin_end = false;  // (TV) by the limit on rejections in a row
+  int cur = -1;           // profile piece of the type's clock
+  uint32_t tries = 0;     // rejections in a row
+
+  // act: the lanes in use, which share the ring's entries.  A resumed lane's
+  // pending arrival is candidate k0 at time t0.
+  __device__ __forceinline__ Arrivals(Lds &lds, int act, bool draws, uint64_t seed_, uint32_t rid_,
+                                      double lam_, int P_, bool resume, double t0, uint32_t k0)
+      : S(lds), tx(threadIdx.x), gl(threadIdx.x & (G - 1)), act_log2(__builtin_ctz(act)), P(P_),
+        seed(seed_), rid(rid_), lam(lam_), tv(TV && P_ > 0), draw_m(ballot(draws)) {
+    const uint32_t depth = min((uint32_t)(RING / 64) * (64u / (uint32_t)act), 64u);
+    dm = depth - 1u;
+    gu = depth / 2u;
+    gu_log2 = __builtin_ctz(gu);
+    if (resume && draws) {  // the pending arrival leads the ring
+      tn = te = tl = t0;
+      kc = k0 + 1u;
+      ended = !(t0 < INFINITY);
+      S.at[slot(0u, tx)] = t0;
+      if constexpr (TV) S.ak[slot(0u, tx)] = k0;
+      re = 1u;
+    }
+  }
+  __device__ __forceinline__ uint32_t slot(uint32_t pos, int ln) const {
+    return ((pos & dm) << act_log2) + (uint32_t)ln;
+  }
+
+  // Every lane of `live` with room for gu draws asks for them and the
+  // wavefront draws all of them together; then each asking lane turns its
+  // gaps into arrival times (with a rate profile, its candidates into the
+  // kept ones).  Every lane of the wavefront takes part.
+  __device__ __forceinline__ void refill(Mask live) {
+    Mask again;
+    do {
+      Mask room = ballot(re - rp <= dm + 1u - gu) & live & draw_m;
+      if constexpr (TV) room &= ~ballot(ended);
+      if (in(room))
+        S.req[__builtin_amdgcn_mbcnt_hi((uint32_t)(room >> 32),
+                                        __builtin_amdgcn_mbcnt_lo((uint32_t)room, 0u))] = (uint8_t)tx;
+      wave_lds_sync();
+      const int total = __popcll(room) << gu_log2;
+      for (int base = 0; base < total; base += 64) {
+        const int w = base + tx;
+        const int ln = (int)S.req[(w < total ? w : 0) >> gu_log2];
+        const uint32_t u = (uint32_t)w & (gu - 1u);
+        // the asking lane's key, rate and counters
+        const uint64_t sd = __shfl(seed, ln, 64);
+        const uint32_t rd = __shfl(rid, ln, 64);
+        const double lm = __shfl(lam, ln, 64);
+        const uint32_t kl = __shfl(kc, ln, 64), el = __shfl(re, ln, 64);
+        uint32_t w3;
+        const double g = draw_gap(sd, rd, (uint32_t)(ln & (G - 1)), kl + u, lm, nullptr, 0, nullptr,
+                                  TV ? &w3 : nullptr);
+        if (w < total) {
+          S.at[slot(el + u, ln)] = g;
+          if constexpr (TV) S.ak[slot(el + u, ln)] = w3;
+        }
+      }
+      wave_lds_sync();
+      if (in(room)) {
+        if (!TV || !tv) {
+          for (uint32_t u = 0; u < gu; u += 4) {  // depth >= 8: gu is a multiple of 4
+            double g[4];
+#pragma unroll
+            for (int x = 0; x < 4; ++x) g[x] = S.at[slot(re + u + (uint32_t)x, tx)];
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+              tl = tl + g[x];
+              S.at[slot(re + u + (uint32_t)x, tx)] = tl;
+              if constexpr (TV) S.ak[slot(re + u + (uint32_t)x, tx)] = kc + u + (uint32_t)x;
+            }
+          }
+          re += gu;
+          te = tl;
+        } else if constexpr (TV) {  // thinning; kept ones move up
+          uint32_t end = re;
+          for (uint32_t u = 0; u < gu && !ended; ++u) {
+            const double g = S.at[slot(re + u, tx)];
+            const uint32_t w3 = S.ak[slot(re + u, tx)];
+            const double fmax = S.prof.fmax[gl];
+            int d = 1;  // no intensity at all: no arrival
+            if (fmax > 0.0) d = thin_decide(tl + g, w3, fmax, S.prof.t, S.prof.f[gl], P, tl, cur);
+            const bool limit = d != 0 && fmax > 0.0 && tries + 1u >= kThinMax;
+            ended = d == 1 || limit;
+            thin_end = thin_end || limit;
+            if (d == 0 || ended) {
+              te = ended ? INFINITY : tl;
+              S.at[slot(end, tx)] = te;
+              S.ak[slot(end, tx)] = kc + u;
+              end++;
+              tries = 0;
+            } else {
+              ++tries;
+            }
+          }
+          re = end;
+        }
+        kc += gu;
+        tn2 = S.at[slot(rp + 1u, tx)];
+      }
+      wave_lds_sync();
+      // thinning may have kept too few: a lane needs the pending arrival, the
+      // next one and the one after it
+      again = 0;
+      if constexpr (TV) again = ballot(re - rp < 3u) & ballot(!ended) & live & draw_m;
+    } while (again != 0);
+  }
+  // The pending arrival and the next one of the lanes of `live`, after the
+  // first refill.
+  __device__ __forceinline__ void start(Mask live) {
+    wave_lds_sync();
+    refill(live);
+    if (in(live & draw_m)) tn = S.at[slot(rp, tx)];
+  }
+  // Lanes whose ring ends with the arrival after the next: to refill before
+  // they move on.
+  __device__ __forceinline__ Mask low() const {
+    Mask m = ballot(rp + 2u >= re) & draw_m;
+    if constexpr (TV) m &= ~ballot(ended);
+    return m;
+  }
+  // This lane's pending arrival has been taken.
+  __device__ __forceinline__ void advance() {
+    rp++;
+    tn = tn2;
+    // (the move first: the read then lands in tn2 itself and is waited for
+    // only when tn2 is used)
+    __builtin_amdgcn_sched_barrier(0);
+    tn2 = S.at[slot(rp + 1u, tx)];
+  }
+  // Did the process end by the limit on rejections (the flag goes up when its
+  // end is reached)?
+  __device__ __forceinline__ bool limited() const { return TV && thin_end && !(tn < INFINITY); }
+  // Back to entry rp0 of the ring (still there: no refill since).
+  __device__ __forceinline__ void rewind(uint32_t rp0) {
+    rp = rp0;
+    tn = S.at[slot(rp, tx)];
+    tn2 = S.at[slot(rp + 1u, tx)];
+  }
+  // Candidate counter of the pending arrival.
+  __device__ __forceinline__ uint32_t pending() const {
+    if constexpr (TV) return S.ak[slot(rp, tx)];
+    return kc - (re - rp);
+  }
+};
+
+// Stage the rate profile of job J in LDS (every lane of the wavefront).
+template <int G, int NP>
+__device__ __forceinline__ void stage_profile(const KArgs &A, const JobDev &J,
+                                              RateProfLds<G, NP> &prof) {
+  const double *rg = (const double *)(A.ws + J.off_rate);
+  const int P = J.n_rate, m = J.m, tx = threadIdx.x;
+  for (int i = tx; i < P; i += 64) prof.t[i] = rg[i];
+  for (int x = tx; x < G * NP; x += 64) {
+    const int j = x / NP, i = x % NP;
+    prof.f[j][i] = j < m && i < P ? rg[P + j * P + i] : 0.0;
+  }
+  for (int j = tx; j < G; j += 64) prof.fmax[j] = j < m ? J.rate_fmax[j] : 0.0;
+}
+
+}  // namespace
+}  // namespace wsim

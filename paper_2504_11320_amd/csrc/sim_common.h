@@ -98,8 +98,8 @@ struct KArgs {
   int32_t lanes;       // replicas per wavefront (lanes >= this are padding)
   int32_t unit_n;      // WAIT launch whose jobs all have thresholds n_j = 1
   int32_t any_caps;    // some job of this launch has per-stage caps
-  int32_t nr;          // WAIT: replicas per wavefront (a divisor of `lanes`)
-  int32_t min_waves;   // WAIT: wavefronts a launch is spread over, if it can be
+  int32_t nr;          // WAIT, FCFS: replicas per wavefront (a divisor of `lanes`)
+  int32_t min_waves;   // WAIT, FCFS: wavefronts a launch is spread over, if it can be
   uint8_t *btrace;     // per-batch trace [R][btrace_cap] records, or null
   int64_t btrace_cap;
 };
@@ -492,45 +492,16 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Opaque copy: stops the compiler from turning a chain of selects over the
-// elements of a register array back into a dynamically indexed access (which
-// would move the array to scratch memory).
+// Opaque copy: a use that the compiler neither moves nor removes (a loaded
+// value is waited for here).
 template <typename T>
 __device__ __forceinline__ T opaque(T x) {
   asm volatile("" : "+v"(x));
   return x;
 }
 
-// a[j] for a lane-dependent j, as selects over the elements.
-template <typename T, int MT>
-__device__ __forceinline__ T pick(const T (&a)[MT], int j) {
-  // the barriers run unconditionally so the choice stays a select
-  T e[MT];
-#pragma unroll
-  for (int i = 0; i < MT; ++i) e[i] = opaque(a[i]);
-  T v = e[0];
-#pragma unroll
-  for (int i = 1; i < MT; ++i) v = (i == j) ? e[i] : v;
-  return v;
-}
-
-// a[j] = v for a lane-dependent j, as selects over the elements.
-template <typename T, int MT>
-__device__ __forceinline__ void place(T (&a)[MT], int j, T v) {
-#pragma unroll
-  for (int i = 0; i < MT; ++i) a[i] = opaque((i == j) ? v : a[i]);
-}
-
-// if (c) a[j] = v, without a branch.
-template <typename T, int MT>
-__device__ __forceinline__ void place_if(T (&a)[MT], int j, bool c, T v) {
-#pragma unroll
-  for (int i = 0; i < MT; ++i) a[i] = opaque((c && i == j) ? v : a[i]);
-}
-
-// Widest wavefront (replicas per wavefront) of the known-length kernel with
-// MT type slots: 64 replicas, 32 with 16 slots (see the note on 16 types in
-// the design notes).
+// Most replicas per row of 64 entries of a known-length launch's replica list
+// with up to mt types (a wavefront takes as many of a row as its lanes hold).
 __host__ __device__ constexpr int known_max_lanes(int mt) { return mt > 8 ? 32 : 64; }
 
 // Launch a simulation kernel on g workgroups of one 64-lane wavefront, after
@@ -563,12 +534,12 @@ __host__ __device__ constexpr int nested_group_width(int max_m, int max_seg) {
 
 // Launchers, one per kernel family (defined next to their kernels).
 hipError_t launch_wait(int max_m, const KArgs &A, hipStream_t s);
-hipError_t launch_known_fcfs(int max_m, const KArgs &A, hipStream_t s);
+hipError_t launch_fcfs(int max_m, const KArgs &A, hipStream_t s);
 hipError_t launch_nested(int max_m, int max_seg, const KArgs &A, hipStream_t s);
 hipError_t launch_fcfs_dist(int max_m, const KArgs &A, hipStream_t s);
 // the kernels for launches with time-varying rates or an arrival list
 hipError_t launch_wait_tv(int max_m, const KArgs &A, hipStream_t s);
-hipError_t launch_known_fcfs_tv(int max_m, const KArgs &A, hipStream_t s);
+hipError_t launch_fcfs_tv(int max_m, const KArgs &A, hipStream_t s);
 hipError_t launch_nested_tv(int max_m, int max_seg, const KArgs &A, hipStream_t s);
 
 }  // namespace wsim

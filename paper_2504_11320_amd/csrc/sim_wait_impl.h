@@ -26,9 +26,9 @@
 // O(events), not O(stages).
 //
 // Arithmetic follows the model contract exactly (same IEEE operations, no FMA
-// contraction): arrivals add their area terms in time order; a batch's
-// completions add their latencies per type in admission order, then the types
-// in turn.
+// contraction): a batch's arrivals and its completions sum their area terms
+// and latencies per type, in time and in admission order, then the types in
+// turn.
 //
 // What bounds it: a replica is a serial chain of events, so a wavefront's
 // latency per batch.  Per wavefront and batch of the Llama-shaped unit
@@ -41,7 +41,7 @@
 // wait after them would wait for them too (17.4 ms).
 #pragma once
 
-#include "sim_lanes.h"
+#include "sim_arrivals.h"
 
 namespace wsim {
 namespace {
@@ -62,15 +62,11 @@ sim_wait_kernel(KArgs A) {
   // at the front of the deque
   constexpr int KQ = ONE ? 1 : 16;
   constexpr int KC = ONE ? 2 : 8;
-  __shared__ double s_at[RING];
-  __shared__ uint32_t s_ak[TV ? RING : 1];  // acceptance words, then candidate indices
+  __shared__ typename Arrivals<G, TV, RING>::Lds s_arr;
   __shared__ DRec s_win[WB][64];
-  __shared__ uint8_t s_req[64];
   __shared__ double s_edges[WS_MAX_HIST_EDGES + 1];
   __shared__ uint8_t s_htab[kHistTab];
   __shared__ int s_hsteps;
-  constexpr int NP = TV ? kMaxRatePts : 1;
-  __shared__ RateProfLds<TV ? G : 1, NP> s_prof;
 
   const int tx = threadIdx.x;
   const int gl = tx & (G - 1);  // lane in the group: type gl
@@ -93,22 +89,13 @@ sim_wait_kernel(KArgs A) {
   const int m = J.m;
   const int n_hist = J.n_hist;
   const int P = TV ? J.n_rate : 0;
-  const bool tv = TV && P > 0;
   const bool trace = TV && J.n_trace > 0;
   const bool is_t = gl < m;
   {
     const double *edges_g = (const double *)(A.ws + J.off_edges);
     for (int b = tx; b <= n_hist; b += 64) s_edges[b] = b < n_hist ? edges_g[b] : INFINITY;
     if constexpr (TV) {
-      if (tv) {
-        const double *rg = (const double *)(A.ws + J.off_rate);
-        for (int i = tx; i < P; i += 64) s_prof.t[i] = rg[i];
-        for (int x = tx; x < G * NP; x += 64) {
-          const int j = x / NP, i = x % NP;
-          s_prof.f[j][i] = j < m && i < P ? rg[P + j * P + i] : 0.0;
-        }
-        for (int j = tx; j < G; j += 64) s_prof.fmax[j] = j < m ? J.rate_fmax[j] : 0.0;
-      }
+      if (P > 0) stage_profile(A, J, s_arr.prof);
     }
     __syncthreads();
   }
@@ -163,18 +150,12 @@ sim_wait_kernel(KArgs A) {
   uint32_t qh, qt, dh, dt, svc, pend, fkc, bkb, bkc;
   int32_t Mj;
   double ba;
-  // Arrival times: the pending one (tn) and the next (tn2) lead the ring of
-  // entries rp .. re-1; kc is the next candidate to draw, tl the clock it
-  // starts from.  rp counts the arrivals taken, ub those of them (and of an
-  // earlier call) that have a first token: rp - ub lack one.
-  double tn = INFINITY, tn2 = INFINITY, tl = 0.0;
-  uint32_t rp = 0, re = 0, kc = 0, ub = 0;
-  bool ended = false;     // (TV) no further arrivals
-  bool thin_end = false;  // (TV) by the limit on rejections in a row
-  int cur = -1;           // profile piece of the type's clock
-  uint32_t tries = 0;     // rejections in a row
-  uint32_t kend = 0;      // candidate counter of a resumed call's pending arrival
-  uint32_t arr_rp = 0;    // rp when `arrivals` was last brought up to date
+  // Of the arrivals taken (in this call, Arrivals::rp) and the earlier ones
+  // without a first token, ub have one by now: rp - ub lack one.
+  uint32_t ub = 0;
+  double t0 = INFINITY;  // a resumed call's pending arrival and its
+  uint32_t k0 = 0;       // candidate counter
+  uint32_t arr_rp = 0;   // rp when `arrivals` was last brought up to date
 
   if (!A.resume) {
     t = lat_area = ttft_area = lat_sum = mem_area = busy = 0.0;
@@ -211,12 +192,9 @@ sim_wait_kernel(KArgs A) {
     svc = (uint32_t)slot_i(A, S_SVC + jt, r);
     Mj = is_t ? (int32_t)slot_i(A, S_MJ + jt, r) : 0;
     pend = is_t ? (uint32_t)slot_i(A, S_LNEXT + jt, r) : 0u;
-    if (is_t) {  // the pending arrival
-      tn = slot_f(A, S_TNEXT + jt, r);
-      kend = (uint32_t)slot_i(A, S_K + jt, r);
-      ended = !(tn < INFINITY);
-      tl = tn;
-      kc = kend + 1u;
+    if (is_t) {
+      t0 = slot_f(A, S_TNEXT + jt, r);
+      k0 = (uint32_t)slot_i(A, S_K + jt, r);
     }
   }
   const int64_t comps0 = comps;
@@ -241,108 +219,11 @@ sim_wait_kernel(KArgs A) {
     bkc = b.kc;
   }
 
-  // ---- draws ------------------------------------------------------------------
-  // the lanes in use share the ring's entries
-  const int act = A.nr * G;
-  const int act_log2 = __builtin_ctz(act);
-  const uint32_t depth = min((uint32_t)(RING / 64) * (64u / (uint32_t)act), 64u);
-  const uint32_t dm = depth - 1u, gu = depth / 2u;  // draws added per request
-  const int gu_log2 = __builtin_ctz(gu);
   const bool draws = valid && is_t && !trace;
-  const Mask draw_m = ballot(draws);
-  auto slot = [&](uint32_t pos, int ln) __attribute__((always_inline)) -> uint32_t {
-    return ((pos & dm) << act_log2) + (uint32_t)ln;
-  };
-  // Every lane with room for gu draws asks for them and the wavefront draws
-  // all of them together; then each asking lane turns its gaps into arrival
-  // times (with a rate profile, its candidates into the kept ones).
-  auto refill = [&]() __attribute__((always_inline)) {
-    Mask again;
-    do {
-      Mask room = ballot(re - rp <= depth - gu) & live & draw_m;
-      if constexpr (TV) room &= ~ballot(ended);
-      if (in(room))
-        s_req[__builtin_amdgcn_mbcnt_hi((uint32_t)(room >> 32),
-                                        __builtin_amdgcn_mbcnt_lo((uint32_t)room, 0u))] = (uint8_t)tx;
-      wave_lds_sync();
-      const int total = __popcll(room) << gu_log2;
-      for (int base = 0; base < total; base += 64) {
-        const int w = base + tx;
-        const int ln = (int)s_req[(w < total ? w : 0) >> gu_log2];
-        const uint32_t u = (uint32_t)w & (gu - 1u);
-        // the asking lane's key, rate and counters
-        const uint64_t sd = __shfl(seed, ln, 64);
-        const uint32_t rd = __shfl(rid, ln, 64);
-        const double lm = __shfl(lam, ln, 64);
-        const uint32_t kl = __shfl(kc, ln, 64), el = __shfl(re, ln, 64);
-        uint32_t w3;
-        const double g = draw_gap(sd, rd, (uint32_t)(ln & (G - 1)), kl + u, lm, nullptr, 0, nullptr,
-                                  TV ? &w3 : nullptr);
-        if (w < total) {
-          s_at[slot(el + u, ln)] = g;
-          if constexpr (TV) s_ak[slot(el + u, ln)] = w3;
-        }
-      }
-      wave_lds_sync();
-      if (in(room)) {
-        if (!TV || !tv) {
-          for (uint32_t u = 0; u < gu; u += 4) {  // depth >= 8: gu is a multiple of 4
-            double g[4];
-#pragma unroll
-            for (int x = 0; x < 4; ++x) g[x] = s_at[slot(re + u + (uint32_t)x, tx)];
-#pragma unroll
-            for (int x = 0; x < 4; ++x) {
-              tl = tl + g[x];
-              s_at[slot(re + u + (uint32_t)x, tx)] = tl;
-              if constexpr (TV) s_ak[slot(re + u + (uint32_t)x, tx)] = kc + u + (uint32_t)x;
-            }
-          }
-          re += gu;
-          kc += gu;
-        } else if constexpr (TV) {  // thinning; kept ones move up
-          uint32_t end = re;
-          for (uint32_t u = 0; u < gu && !ended; ++u) {
-            const double g = s_at[slot(re + u, tx)];
-            const uint32_t w3 = s_ak[slot(re + u, tx)];
-            const double fmax = s_prof.fmax[gl];
-            int d = 1;  // no intensity at all: no arrival
-            if (fmax > 0.0) d = thin_decide(tl + g, w3, fmax, s_prof.t, s_prof.f[gl], P, tl, cur);
-            const bool limit = d != 0 && fmax > 0.0 && tries + 1u >= kThinMax;
-            ended = d == 1 || limit;
-            thin_end = thin_end || limit;
-            if (d == 0 || ended) {
-              s_at[slot(end, tx)] = ended ? INFINITY : tl;
-              s_ak[slot(end, tx)] = kc + u;
-              end++;
-              tries = 0;
-            } else {
-              ++tries;
-            }
-          }
-          re = end;
-          kc += gu;
-        }
-      }
-      wave_lds_sync();
-      // thinning may have kept too few: a lane needs the pending arrival, the
-      // next one and the one after it
-      again = 0;
-      if constexpr (TV) again = ballot(re - rp < 3u) & ballot(!ended) & live & draw_m;
-    } while (again != 0);
-  };
-  if (A.resume && draws) {  // the pending arrival leads the ring
-    s_at[slot(0u, tx)] = tn;
-    if constexpr (TV) s_ak[slot(0u, tx)] = kend;
-    re = 1u;
-  }
+  Arrivals<G, TV, RING> arr(s_arr, A.nr * G, draws, seed, rid, lam, P, A.resume != 0, t0, k0);
   if (!trace) {
-    wave_lds_sync();
-    refill();
-    if (in(live & draw_m)) {
-      tn = s_at[slot(rp, tx)];
-      tn2 = s_at[slot(rp + 1u, tx)];
-      if (TV && thin_end && !(tn < INFINITY)) flags |= kFlagThin;
-    }
+    arr.start(live);
+    if (draws && !A.resume && arr.limited()) flags |= kFlagThin;
   }
 
   // ---- arrivals ---------------------------------------------------------------
@@ -356,15 +237,15 @@ sim_wait_kernel(KArgs A) {
         return ta;
       }
     }
-    const double ta = group_min<G>(tn);
-    mine = ballot(tn == ta);
+    const double ta = group_min<G>(arr.tn);
+    mine = ballot(arr.tn == ta);
     return ta;
   };
   // One arrival of each group in `go` joins its queue: the lane in `mine` (of
   // simultaneous ones the lowest) takes it at time ta and moves to its
   // type's next arrival.  A group whose queue was full (it ends at its next
-  // decision) leaves `more`.
-  auto take = [&](Mask go, Mask mine, double ta, Mask &more) __attribute__((always_inline)) {
+  // decision) leaves `more`.  Returns the lanes that took one.
+  auto take = [&](Mask go, Mask mine, double ta, Mask &more) __attribute__((always_inline)) -> Mask {
     Mask me = go & mine;
     if constexpr (G > 1) {
       if (__popcll(me) * G != __popcll(go)) me = group_lowest<G>(me);
@@ -372,23 +253,21 @@ sim_wait_kernel(KArgs A) {
     if constexpr (TV) {
       if (trace && in(go)) tridx++;
     }
-    // rare: the ring ends with the arrival after the next, or the queue is full
-    Mask low = ballot(rp + 2u >= re) & draw_m;
-    if constexpr (TV) low &= ~ballot(ended);
+    // rare: the ring of arrival times runs low, or the queue is full
+    const Mask low = arr.low();
     const Mask full = ballot(qt - qh >= rec_cap);
     if ((me & (low | full)) != 0) {
       if (in(me & full)) flags |= kFlagCap;
       more &= ~group_spread<G>(me & full);
-      if ((me & low) != 0) refill();
+      if ((me & low) != 0) arr.refill(live);
     }
     if (in(me)) {
       qr[qt & qmask] = ta;  // a full queue is not read again
       qt++;
-      rp++;
-      tn = tn2;
-      tn2 = s_at[slot(rp + 1u, tx)];
-      if (TV && thin_end && !(tn < INFINITY)) flags |= kFlagThin;
+      arr.advance();
+      if (arr.limited()) flags |= kFlagThin;
     }
+    return me;
   };
 
   // This batch's admissions join the deque: the x-th of them is stored; then
@@ -440,8 +319,8 @@ sim_wait_kernel(KArgs A) {
   int64_t it = 0;
   for (; it < A.horizon; ++it) {
     if ((it & 255) == 255) {  // 32-bit counts to 64 bits
-      arrivals += rp - arr_rp;
-      arr_rp = rp;
+      arrivals += arr.rp - arr_rp;
+      arr_rp = arr.rp;
       comps += comp32;
       comp32 = 0;
       evicts += evict32;
@@ -473,7 +352,7 @@ sim_wait_kernel(KArgs A) {
         wait &= ~none;
       }
       const int32_t N = group_sum32<G>((int32_t)((qt - qh) + (dt - dh)));
-      const int32_t U = group_sum32<G>((int32_t)(rp - ub));
+      const int32_t U = group_sum32<G>((int32_t)(arr.rp - ub));
       if (in(wait)) {
         const double dtm = ta - t;
         lat_area += (double)N * dtm;
@@ -495,7 +374,7 @@ sim_wait_kernel(KArgs A) {
     const uint32_t bidx = (uint32_t)(batches0 + it);
     const uint32_t now = svc + 1u;
     const int32_t N0 = group_sum32<G>((int32_t)((qt - qh) + (dt - dh)));
-    const int32_t U0 = group_sum32<G>((int32_t)(rp - ub));
+    const int32_t U0 = group_sum32<G>((int32_t)(arr.rp - ub));
     uint32_t na = nowait ? min(qt - qh, (uint32_t)nth) : (uint32_t)ncap;
     na = in(served) ? na : 0u;
     // the deque's front completes in this batch (prompts admitted now never do)
@@ -550,25 +429,73 @@ sim_wait_kernel(KArgs A) {
     qh += na;
 
     // ---- arrivals during the batch ----------------------------------------
+    // Each type takes its own, in time order, and sums their area terms; the
+    // sums join the areas in type order.  Types need no order between them
+    // but where a queue overflows: that ends the group's arrivals at its
+    // instant.
     Mask inb = live;
-    for (;;) {
-      Mask mine;
-      const double ta = peek(mine);
-      const Mask go = ballot(ta <= t_end) & inb;
-      if (go == 0) break;
-      const double w = in(go) ? t_end - ta : 0.0;  // (areas are never -0)
-      lat_area += w;
-      ttft_area += w;
-      take(go, mine, ta, inb);
+    double part_a = 0.0;
+    auto in_order = [&](Mask who, double tm) __attribute__((always_inline)) {
+      for (;;) {
+        Mask mine;
+        const double ta = peek(mine);
+        const Mask go = ballot(ta <= t_end) & ballot(ta < tm) & who & inb;
+        if (go == 0) break;
+        const Mask me = take(go, mine, ta, inb);
+        part_a += in(me) ? t_end - ta : 0.0;
+      }
+    };
+    if (TV && trace) {
+      in_order(live, INFINITY);
+    } else {
+      for (;;) {
+        // up to what every ring of the group knows
+        double tm = group_min<G>(arr.te);
+        Mask more = ballot(tm <= t_end) & inb;
+        if (more != 0) {
+          arr.refill(live);
+          tm = group_min<G>(arr.te);
+          more = ballot(tm <= t_end) & inb;
+        }
+        const uint32_t qt0 = qt, rp0 = arr.rp;
+        const double pa0 = part_a;
+        Mask run = ballot(arr.tn <= t_end) & ballot(arr.tn < tm) & inb;
+        while (run != 0) {
+          if (in(run)) {
+            part_a += t_end - arr.tn;
+            qr[qt & qmask] = arr.tn;
+            qt++;
+            arr.advance();
+            if (arr.limited()) flags |= kFlagThin;
+          }
+          run &= ballot(arr.tn <= t_end) & ballot(arr.tn < tm);
+        }
+        const Mask full = ballot(qt - qh > rec_cap) & inb;
+        if (full != 0) {  // rare: again in time order, up to the overflow
+          const Mask again = group_spread<G>(full);
+          if (in(again)) {
+            qt = qt0;
+            part_a = pa0;
+            if (draws) arr.rewind(rp0);
+          }
+          in_order(again, tm);
+        }
+        if (more == 0) break;
+      }
     }
-    if (in(live)) {
-      lat_area += (double)N0 * tau;
-      ttft_area += (double)U0 * tau;
-      mem_area += (double)m_launch * tau;
-      busy += tau;
-      t = t_end;
-      peak = max(peak, m_launch);
-      btok += tokens;
+    {
+      const double sum = add_in_order<G>(0.0, part_a, ballot(part_a != 0.0));
+      if (in(live)) {
+        lat_area += sum;
+        ttft_area += sum;
+        lat_area += (double)N0 * tau;
+        ttft_area += (double)U0 * tau;
+        mem_area += (double)m_launch * tau;
+        busy += tau;
+        t = t_end;
+        peak = max(peak, m_launch);
+        btok += tokens;
+      }
     }
 
     // ---- completion transition ----------------------------------------------
@@ -774,11 +701,11 @@ sim_wait_kernel(KArgs A) {
   evicts += evict32;
   batches = batches0 + (stop >= 0 ? stop : it);
   const int64_t ctok = group_sum<G>((comps - comps0) * lp + ctok0);
-  arrivals = group_sum<G>(arrivals + (int64_t)(rp - arr_rp));
+  arrivals = group_sum<G>(arrivals + (int64_t)(arr.rp - arr_rp));
   comps = group_sum<G>(comps);
   evicts = group_sum<G>(evicts);
   etok = group_sum<G>(etok);
-  const int32_t U = group_sum32<G>((int32_t)(rp - ub));
+  const int32_t U = group_sum32<G>((int32_t)(arr.rp - ub));
   const int32_t N = group_sum32<G>((int32_t)((qt - qh) + (dt - dh)));
   flags = group_or<G>(flags);
   if (!valid) return;
@@ -809,13 +736,8 @@ sim_wait_kernel(KArgs A) {
     put_i(A, S_FLAGS, r, (int64_t)flags);
   }
   if (is_t) {
-    put_f(A, S_TNEXT + gl, r, tn);
-    uint32_t kp = kend;  // candidate counter of the pending arrival
-    if (draws) kp = kc - (re - rp);
-    if constexpr (TV) {
-      if (draws) kp = s_ak[slot(rp, tx)];
-    }
-    put_i(A, S_K + gl, r, kp);
+    put_f(A, S_TNEXT + gl, r, draws ? arr.tn : t0);
+    put_i(A, S_K + gl, r, draws ? arr.pending() : k0);
     put_i(A, S_QH + gl, r, qh);
     put_i(A, S_QT + gl, r, qt);
     put_i(A, S_DH + gl, r, dh);

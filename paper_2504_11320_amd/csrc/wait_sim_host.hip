@@ -235,23 +235,26 @@ int guarded(F &&body) noexcept {
   }
 }
 
-// Replicas per 64-lane wavefront.  A replica is a serial chain of events, so
-// a wavefront's time per batch is set by latency, not by how many of its lanes
-// are busy: when a launch has few replicas they are spread over more
-// wavefronts (64, 32, 16 or 8 per wavefront; Nested WAIT 32 down to 4) until
-// the launch has at least the target number of wavefronts or reaches the
-// smallest width.  The WAIT/FCFS kernel targets one wavefront per SIMD (1024):
-// a second one per SIMD gains nothing there; with time-varying rates (longer
-// chains of dependent LDS reads per arrival) it targets two per SIMD.  The
-// Nested WAIT kernel, which waits on dependent loads of records, targets two
-// per SIMD (2048).  A wavefront never has more lanes than the largest job has replicas
-// (fewer lanes, less LDS).
+// Replicas per row of 64 entries of a launch's replica list.  A replica is a
+// serial chain of events, so a wavefront's time per batch is set by latency,
+// not by how many of its lanes are busy: when a launch has few replicas they
+// are spread over more rows (64, 32, 16 or 8 per row; Nested WAIT 32 down to
+// 4) until there are the target number of them, or the smallest width is
+// reached.  A row never has more replicas than the largest job.  The kernel
+// for drawn output lengths and the Nested WAIT kernel run a row to a wavefront.
+// The WAIT and FCFS kernels split a row over as many wavefronts as their lane
+// groups need, and halve a wavefront's replicas further while the launch has
+// fewer than kMinWavesLanes wavefronts, one per SIMD: at 2,107 replicas in 7
+// jobs (a checkpointed continuation, 1,500 batches) 1,024 wavefronts took 2.50
+// ms, 512 took 2.59, 256 took 2.82 and 2,048 3.45; at 2 x 9,216 replicas of one
+// type (1,000 batches) 1,024 of each policy took 13.3 ms and 2,048 16.1.  The
+// list is part of a checkpoint's fingerprint, so its layout is kept.
 #ifndef WS_TARGET_WAVES
 #define WS_TARGET_WAVES 1024
 #endif
 constexpr int64_t kTargetWaves = WS_TARGET_WAVES;
 constexpr int64_t kTargetWavesNested = 2 * WS_TARGET_WAVES;
-constexpr int32_t kMinWavesWait = 2048;
+constexpr int32_t kMinWavesLanes = WS_TARGET_WAVES;
 
 int ceil_log2(uint64_t x) {
   int k = 0;
@@ -615,9 +618,7 @@ int make_layout(const ws_job *jobs, int32_t n_jobs, Layout &Lo, JobHost *storage
     int32_t nmax = 0;  // largest job: no wavefront needs more lanes
     for (int i = 0; i < n_jobs; ++i)
       if (launch_kind(jobs[i]) == pk) nmax = std::max(nmax, jobs[i].n);
-    // the known-length kernels with up to 4 types stop at 32 replicas per
-    // wavefront (their 64-lane LDS footprint would leave half of a CU's SIMDs
-    // idle), except replays
+    // (known lengths: 32 replicas to a row with up to 4 types, except replays)
     int lanes = Lo.max_m[pk] <= 4 && !any_trace ? 32 : known_max_lanes(Lo.max_m[pk]);
     const int min_lanes = 8;
     bool any_tv = false;
@@ -625,11 +626,11 @@ int make_layout(const ws_job *jobs, int32_t n_jobs, Layout &Lo, JobHost *storage
       any_tv |= launch_kind(jobs[i]) == pk && jobs[i].cfg->n_rate_pts > 0;
     const int64_t target = any_tv ? kTargetWavesNested : kTargetWaves;
     if (pk == kFcfsDist) lanes = 64;  // per-lane state in registers and LDS columns
-    if (pk == WS_WAIT && Lo.max_m[pk] > WS_MAX_TYPES_KNOWN) lanes = 16;  // LDS columns
+    if (pk == WS_WAIT && Lo.max_m[pk] > WS_MAX_TYPES_KNOWN) lanes = 16;
     if (pk == WS_NESTED_WAIT) {
       // a group of lanes per replica: 64 / G replicas per wavefront
       lanes = 64 / nested_group_width(Lo.max_m[pk], Lo.max_seg);
-    } else if (!any_trace) {  // known-length replays keep the widest
+    } else if (!any_trace) {  // replays keep the widest
       while (lanes > min_lanes && lanes / 2 >= nmax) lanes /= 2;
       while (lanes > min_lanes && waves(lanes) < target) lanes /= 2;
     }
@@ -880,7 +881,7 @@ int advance_impl(const ws_job *jobs, int32_t n_jobs, const Layout &Lo, int64_t h
     B.off_list = Lo.list_off[pk];
     B.n_list = Lo.list_count[pk];
     B.lanes = Lo.lanes[pk];
-    B.min_waves = kMinWavesWait;
+    B.min_waves = kMinWavesLanes;
     B.any_trace = B.any_tv = B.any_caps = 0;
     B.unit_n = pk == WS_WAIT ? 1 : 0;
     for (int i = 0; i < n_jobs; ++i) {
@@ -900,7 +901,7 @@ int advance_impl(const ws_job *jobs, int32_t n_jobs, const Layout &Lo, int64_t h
       e = launch_fcfs_dist(Lo.max_m[pk], B, ls);
     else
       e = pk == WS_WAIT ? launch_wait(Lo.max_m[pk], B, ls)
-                        : launch_known_fcfs(Lo.max_m[pk], B, ls);
+                        : launch_fcfs(Lo.max_m[pk], B, ls);
     if (e != hipSuccess) return fail(WS_EDEVICE, std::string("launch: ") + hipGetErrorString(e));
     launched++;
   }
