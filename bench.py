@@ -55,9 +55,11 @@ PROFILES = {
                     ("sim_wait_impl.h", "sim_arrivals.h", "sim_lanes.h", "sim_wait_tv.hip",
                      "sim_common.h")),
     "nested-geometric": ("sim_nested_3type_geometric_32x1024x1e5",
-                         ("sim_nested_impl.h", "sim_lanes.h", "sim_nested.hip", "sim_common.h")),
+                         ("sim_nested_unit_impl.h", "sim_arrivals.h", "sim_lanes.h",
+                          "sim_nested_unit.hip", "sim_common.h")),
     "nested-heavytail": ("sim_nested_10type_lognormal_8192x1e6",
-                         ("sim_nested_impl.h", "sim_lanes.h", "sim_nested.hip", "sim_common.h")),
+                         ("sim_nested_unit_impl.h", "sim_arrivals.h", "sim_lanes.h",
+                          "sim_nested_unit.hip", "sim_common.h")),
     "fcfs-chunked": ("sim_known_fcfs_3type_chunk512_32x1024x1e5",
                      ("sim_fcfs_impl.h", "sim_arrivals.h", "sim_lanes.h", "sim_fcfs.hip", "sim_common.h")),
 }
@@ -385,7 +387,7 @@ def main() -> int:
                 "hbm_measured_frac": (traffic * args.steps / secs / HBM_PEAK
                                       if traffic is not None else None),
                 "launches": args.steps,
-                "kernel": (f"sim_nested_kernel ({m} types)" if policy == "nested"
+                "kernel": (f"sim_nested_unit_kernel ({m} types)" if policy == "nested"
                            else f"sim_wait_kernel ({m} types)" if policy.startswith("wait")
                            else f"sim_fcfs_kernel ({m} types)")
                           + (f", time-varying rates ({rate_pts} points, "

@@ -15,7 +15,7 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 SRC_NAMES = ("wait_sim_host.hip", "sim_wait.hip", "sim_fcfs.hip",
-             "sim_nested.hip", "sim_wait_tv.hip", "sim_fcfs_tv.hip",
+             "sim_nested.hip", "sim_nested_unit.hip", "sim_wait_tv.hip", "sim_fcfs_tv.hip",
              "sim_nested_tv.hip", "sim_fcfs_dist.hip")
 SRCS = [os.path.join(CSRC, f) for f in SRC_NAMES]
 INC = os.path.join(ROOT, "include")
@@ -37,6 +37,7 @@ HIPCC_FLAGS = [
 SCHED_FLAGS = {
     "sim_wait.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"],
     "sim_wait_tv.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"],
+    "sim_nested_unit.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"],
     "sim_nested.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"],
     "sim_nested_tv.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"],
 }

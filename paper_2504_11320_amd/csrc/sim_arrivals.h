@@ -9,13 +9,23 @@
 namespace wsim {
 namespace {
 
-// TV: rate profiles are supported.  RING: ring entries of a wavefront.
-template <int G, bool TV, int RING>
+// Output lengths drawn with the arrivals: CDF rows, their cap, search guide.
+struct LenLaw {
+  const uint32_t *cdf;
+  int32_t cap;  // <= 1: no draw, every length is 1; at most 65535
+  const uint16_t (*guide)[kCdfGuide + 1];
+};
+
+// TV: rate profiles are supported.  RING: ring entries of a wavefront.  LEN:
+// output lengths are drawn too (law; constant rates only).
+template <int G, bool TV, int RING, bool LEN = false>
 struct Arrivals {
+  static_assert(!TV || !LEN, "lengths are drawn at constant rates");
   static constexpr int NP = TV ? kMaxRatePts : 1;
   struct Lds {
     double at[RING];
     uint32_t ak[TV ? RING : 1];  // acceptance words, then candidate indices
+    uint16_t len[LEN ? RING : 1];
     RateProfLds<TV ? G : 1, NP> prof;
     uint8_t req[64];
   };
@@ -36,6 +46,7 @@ struct Arrivals {
   bool thin_end = false;  // (TV) by the limit on rejections in a row
   int cur = -1;           // profile piece of the type's clock
   uint32_t tries = 0;     // rejections in a row
+  LenLaw law = {nullptr, 0, nullptr};
 
   // act: the lanes in use, which share the ring's entries.  A resumed lane's
   // pending arrival is candidate k0 at time t0.
@@ -84,10 +95,20 @@ struct Arrivals {
         const double lm = __shfl(lam, ln, 64);
         const uint32_t kl = __shfl(kc, ln, 64), el = __shfl(re, ln, 64);
         uint32_t w3;
-        const double g = draw_gap(sd, rd, (uint32_t)(ln & (G - 1)), kl + u, lm, nullptr, 0, nullptr,
-                                  TV ? &w3 : nullptr);
+        int32_t len = 1;
+        const int j = ln & (G - 1);
+        const uint32_t *row = nullptr;
+        const uint16_t *guide = nullptr;
+        if constexpr (LEN) {
+          if (law.cap > 1) row = law.cdf + (size_t)j * (size_t)(law.cap - 1);
+          if (law.guide != nullptr) guide = law.guide[j];
+        }
+        const double g = draw_gap(sd, rd, (uint32_t)j, kl + u, lm, LEN ? row : nullptr,
+                                  LEN ? law.cap : 0, LEN ? &len : nullptr, TV ? &w3 : nullptr,
+                                  LEN ? guide : nullptr);
         if (w < total) {
           S.at[slot(el + u, ln)] = g;
+          if constexpr (LEN) S.len[slot(el + u, ln)] = (uint16_t)len;
           if constexpr (TV) S.ak[slot(el + u, ln)] = w3;
         }
       }

@@ -96,7 +96,7 @@ struct KArgs {
   int32_t any_trace;   // some job of this launch replays a fixed arrival list
   int32_t any_tv;      // some job of this launch has time-varying rates
   int32_t lanes;       // replicas per wavefront (lanes >= this are padding)
-  int32_t unit_n;      // WAIT launch whose jobs all have thresholds n_j = 1
+  int32_t unit_n;      // WAIT or Nested WAIT launch whose thresholds are all 1
   int32_t any_caps;    // some job of this launch has per-stage caps
   int32_t nr;          // WAIT, FCFS: replicas per wavefront (a divisor of `lanes`)
   int32_t min_waves;   // WAIT, FCFS: wavefronts a launch is spread over, if it can be
@@ -536,6 +536,7 @@ __host__ __device__ constexpr int nested_group_width(int max_m, int max_seg) {
 hipError_t launch_wait(int max_m, const KArgs &A, hipStream_t s);
 hipError_t launch_fcfs(int max_m, const KArgs &A, hipStream_t s);
 hipError_t launch_nested(int max_m, int max_seg, const KArgs &A, hipStream_t s);
+hipError_t launch_nested_unit(int max_m, int max_seg, const KArgs &A, hipStream_t s);
 hipError_t launch_fcfs_dist(int max_m, const KArgs &A, hipStream_t s);
 // the kernels for launches with time-varying rates or an arrival list
 hipError_t launch_wait_tv(int max_m, const KArgs &A, hipStream_t s);

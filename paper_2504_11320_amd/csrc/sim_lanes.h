@@ -132,39 +132,41 @@ __device__ constexpr Mask group_leaders() {
   for (int i = 0; i < 64; i += G) m |= 1ull << i;
   return m;
 }
-// Lanes x of every group with x + d < G (they have a lane d above them).
+// This lane's group, and the lanes of it below this one.  With these two
+// kept per lane a question about a group of a mask is three vector
+// instructions; on the scalar unit it would be a chain of shifts.
 template <int G>
-__device__ constexpr Mask group_below(int d) {
-  Mask m = 0;
-  for (int i = 0; i < 64; ++i)
-    if ((i & (G - 1)) + d < G) m |= 1ull << i;
-  return m;
+__device__ __forceinline__ Mask group_of_lane() {
+  return (G == 64 ? ~0ull : (1ull << (G & 63)) - 1ull) << (threadIdx.x & (64 - G));
 }
+template <int G>
+__device__ __forceinline__ Mask below_lane() {
+  return group_of_lane<G>() & ((1ull << threadIdx.x) - 1ull);
+}
+// (Every lane of the wavefront takes part in these.)
 // All lanes of the groups that have a lane in m.
 template <int G>
 __device__ __forceinline__ Mask group_spread(Mask m) {
-  if constexpr (G == 64) return m != 0 ? ~0ull : 0ull;
-#pragma unroll
-  for (int d = 1; d < G; d *= 2) m |= m >> d;
-  m &= group_leaders<G>();
-  return (m << (G & 63)) - m;
+  if constexpr (G == 1) return m;
+  return ballot((m & group_of_lane<G>()) != 0);
 }
 // The lowest and the highest lane of m in every group.
 template <int G>
 __device__ __forceinline__ Mask group_lowest(Mask m) {
-  Mask below = G > 1 ? (m & group_below<G>(1)) << 1 : 0;  // lanes with one of m below them
-#pragma unroll
-  for (int d = 1; d < G / 2; d *= 2) below |= (below & group_below<G>(d)) << d;
-  if constexpr (G >= 4) below |= (below & group_below<G>(G / 2)) << (G / 2);
-  return m & ~below;
+  if constexpr (G == 1) return m;
+  return m & ballot((m & below_lane<G>()) == 0);
 }
 template <int G>
 __device__ __forceinline__ Mask group_highest(Mask m) {
-  Mask above = G > 1 ? (m >> 1) & group_below<G>(1) : 0;  // lanes with one of m above them
-#pragma unroll
-  for (int d = 1; d < G / 2; d *= 2) above |= (above >> d) & group_below<G>(d);
-  if constexpr (G >= 4) above |= (above >> (G / 2)) & group_below<G>(G / 2);
-  return m & ~above;
+  if constexpr (G == 1) return m;
+  const Mask above = group_of_lane<G>() & ~((2ull << threadIdx.x) - 1ull);
+  return m & ballot((m & above) == 0);
+}
+// Lanes with one of m at or below them in their group.
+template <int G>
+__device__ __forceinline__ Mask group_fill_up(Mask m) {
+  if constexpr (G == 1) return m;
+  return ballot((m & group_of_lane<G>() & ((2ull << threadIdx.x) - 1ull)) != 0);
 }
 
 // The group's G bits of a wavefront ballot (bit g = group lane g).

@@ -35,13 +35,13 @@
 // list of the prompts that exit at that service.  Cohorts are linked in
 // reverse admission order, so a bucket is traversed youngest cohort first and
 // in admission order within a cohort: the same (stage, key) order as the
-// oracle's selection list.  The completion latencies a segment lane meets are
-// buffered in LDS and added to the replica's latency sum in segment order, so
-// the floating-point sum takes the oracle's order exactly.
+// oracle's selection list.  A segment lane sums the latencies it meets; the
+// segments' sums join the replica's in segment order.
 //
 // The projected state Q+ of the pre-launch repair (apply the selected moves
 // with no early completion) is computed from per-segment counts and the
-// prompts still live in the terminal cohort slot (a record with L = 0 has left
+// prompts still live in the terminal cohort slot (those that stay to the
+// segment's end, L >= r_k; a record with L = 0 has left
 // its segment).
 //
 // Memory handoffs between lanes of one wavefront (a survivor pushed by lane k
@@ -117,8 +117,6 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) si
   constexpr int GR = TV || G > 32 ? 4 : 8;
   constexpr int GU = GR / 2;         // draws added per refill
   constexpr uint32_t kLow = GU / 2;  // a ring below this triggers a refill
-  // completion latencies buffered per segment lane before they are summed
-  constexpr int KL = 8;
   __shared__ double s_gap[MT][GR][NR];
   __shared__ int32_t s_glen[MT][GR][NR];
   constexpr int NP = TV ? kMaxRatePts : 1;
@@ -135,10 +133,6 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) si
   __shared__ double s_lam[MT];
   __shared__ int32_t s_l[MT], s_lp[MT];
   __shared__ SegConst s_seg[LT];
-  // completion latencies of one batch, per segment, in traversal order
-  __shared__ double s_lat[LT][KL][NR];
-  __shared__ int32_t s_latn[LT][NR];
-  __shared__ int32_t s_latdone[LT][NR];
   __shared__ uint16_t s_cdfg[MT][kCdfGuide + 1];
   __shared__ double s_edges[WS_MAX_HIST_EDGES + 1];
   __shared__ uint8_t s_htab[kHistTab];
@@ -544,11 +538,12 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) si
     }
     for (; back < delta && (int64_t)svc - back >= 1; ++back, ifrom = nrow - 1) {
       const uint32_t slot = fastmod(svc - (uint32_t)back, dmg, (uint32_t)delta);
-      // a record with L = 0 has left the segment (exit or eviction)
+      // (the kernel for unit thresholds marks evictions only, not exits)
       for (int32_t i = ifrom; i >= 0; --i) {
         const uint32_t idx = slot * (uint32_t)nrow + (uint32_t)i;
         const NRec rec = load_nrec(rc + idx);
-        if (rec.L != 0) {
+        // live: not evicted, and its exit (after min(L, r_k)) is to come
+        if (rec.L != 0 && rec.c + (uint32_t)((rec.L < rk ? rec.L : rk) - ent) > svc) {
           yi = rec;
           yidx = idx;
           return idx;
@@ -854,15 +849,15 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) si
           // the terminal cohort slot: its prompts still in the segment
           if (nrow == 1) {  // prefetched
             const int32_t trL = (int32_t)pf_tr.y, trj = (int32_t)pf_tr.x;
-            T = trL != 0 ? 1u : 0u;
-            Tl = trL != 0 ? (uint32_t)plen(trj) : 0u;
+            T = trL >= rk ? 1u : 0u;  // it stays to the segment's end
+            Tl = trL >= rk ? (uint32_t)plen(trj) : 0u;
           } else {
             const uint32_t ts = slot_after(slot);  // x - (delta - 1) = x + 1 mod delta
             for (int32_t i = 0; i < nrow; ++i) {
               // j and L (the second half's first two words) in one load
               const uint2 jl = *(const uint2 *)((const uint8_t *)(rc + ts * (uint32_t)nrow +
                                                                   (uint32_t)i) + 16);
-              const bool live = (int32_t)jl.y != 0;
+              const bool live = (int32_t)jl.y >= rk;
               T += live ? 1u : 0u;
               Tl += live ? (uint32_t)plen((int32_t)jl.x) : 0u;
             }
@@ -958,11 +953,9 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) si
       bk[xs] = kNil;
     }
     wave_lds_sync();
-    // Walk the buckets served now.  A lane stops after KL completions until
-    // the group's latency sum has taken them: the sum runs over segments in
-    // order, each segment's latencies in traversal order.
-    // survivors join the back of segment k+1's boundary queue: its ring ends,
-    // from lane k+1; what was pushed goes to lane k+1 after the walk
+    // Walk the buckets served now.  Survivors join the back of segment k+1's
+    // boundary queue: its ring ends, from lane k+1; what was pushed goes to
+    // lane k+1 after the walk.
     const uint32_t vtn = seg_next<G>(vt), vhn = seg_next<G>(vh);
     uint32_t npush = 0;
     int32_t bpush = 0;
@@ -977,91 +970,70 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) si
         crec = load_nrec(rc + node);
     }
     __builtin_amdgcn_s_setprio(2);  // the walk (see the pre-launch repair)
-    int32_t nbuf = 0;
+    double part = 0.0;  // the segment's latencies in traversal order
     // a bucket lists at most the segment's delta_k * n_k records: a longer
     // walk could only follow a corrupted link, so it stops the replica
     uint32_t steps = 0;
     const uint32_t max_steps = (uint32_t)delta * (uint32_t)nrow;
-    for (;;) {
-      while (node != kNil && nbuf < KL) {
-        if (++steps > max_steps) {
-          lflags |= kFlagCap;
-          node = kNil;
-          break;
-        }
-        const NRec rec = crec;
-        const uint32_t nxt = rec.next;
-        if (nxt != kNil) {  // one node ahead
-          if (pre_ok && nxt == bh0)
-            crec = crec0;
-          else
-            crec = load_nrec(rc + nxt);
-        }
-        if (rec.L != 0) {  // holes left by evictions are skipped
-          if (!TV && node == y2idx) y2idx = kNil;  // the second leaves
-          if (node == yidx) {  // the youngest leaves
-            if (!TV && y2idx != kNil) {  // the second is the new youngest
-              yi = y2;
-              yidx = y2idx;
-              y2idx = kNil;
-            } else {
-              ydead = node;
-              yidx = kNil;
-            }
-          }
-          const int64_t le = plen(rec.j);
-          const int32_t p = rec.L < rk ? rec.L : rk;
-          if (rec.c != x) {  // an interior prompt: it had advanced to p + 1
-            Mk -= le + p + 1;
-            Ik -= 1u;
-          }
-          if (rec.L == p) {  // completion at its own output length
-            const double lat = t_end - arrival_of(rec.a_ft);
-            s_lat[k][nbuf][q] = lat;
-            nbuf++;
-            __hip_atomic_fetch_add(&hist[hist_bin_idx(edges, s_htab, hidx, lat)], 1u,
-                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            dcomp++;
-            dctok += rec.L;
-          } else {  // survivor joins the boundary queue of segment k+1
-            NRec v = rec;
-            v.a_ft = with_ft(rec.a_ft);
-            const uint32_t vp = vtn + npush;
-            if (vp - vhn <= vmaskn) {
-              vrn[vp & vmaskn] = v;
-              npush++;
-              vlast = v;
-            } else {
-              lflags |= kFlagCap;  // bounded by construction; guards the ring
-            }
-            bpush += (int32_t)(le + rk);
-            dM += (int32_t)(le + rk);
-          }
-          rc[node].L = 0;  // no longer in the segment
-        }
-        node = nxt;
+    while (node != kNil) {
+      if (++steps > max_steps) {
+        lflags |= kFlagCap;
+        node = kNil;
+        break;
       }
-      // the group's latency sum takes the buffered latencies in segment order,
-      // up to the first segment still walking
-      if (group_bits<G>(nbuf != 0) != 0) {
-        if (is_s) {
-          s_latn[k][q] = nbuf;
-          s_latdone[k][q] = node == kNil ? 1 : 0;
-        }
-        wave_lds_sync();
-        if (gl == 0) {
-          for (int kk = 0; kk < kmax; ++kk) {
-            const int32_t nb = s_latn[kk][q];
-            for (int32_t i = 0; i < nb; ++i) lat_sum += s_lat[kk][i][q];
-            s_latn[kk][q] = 0;
-            if (!s_latdone[kk][q]) break;
+      const NRec rec = crec;
+      const uint32_t nxt = rec.next;
+      if (nxt != kNil) {  // one node ahead
+        if (pre_ok && nxt == bh0)
+          crec = crec0;
+        else
+          crec = load_nrec(rc + nxt);
+      }
+      if (rec.L != 0) {  // holes left by evictions are skipped
+        if (!TV && node == y2idx) y2idx = kNil;  // the second leaves
+        if (node == yidx) {  // the youngest leaves
+          if (!TV && y2idx != kNil) {  // the second is the new youngest
+            yi = y2;
+            yidx = y2idx;
+            y2idx = kNil;
+          } else {
+            ydead = node;
+            yidx = kNil;
           }
         }
-        wave_lds_sync();
-        if (is_s) nbuf = s_latn[k][q];
+        const int64_t le = plen(rec.j);
+        const int32_t p = rec.L < rk ? rec.L : rk;
+        if (rec.c != x) {  // an interior prompt: it had advanced to p + 1
+          Mk -= le + p + 1;
+          Ik -= 1u;
+        }
+        if (rec.L == p) {  // completion at its own output length
+          const double lat = t_end - arrival_of(rec.a_ft);
+          part += lat;
+          __hip_atomic_fetch_add(&hist[hist_bin_idx(edges, s_htab, hidx, lat)], 1u,
+                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          dcomp++;
+          dctok += rec.L;
+        } else {  // survivor joins the boundary queue of segment k+1
+          NRec v = rec;
+          v.a_ft = with_ft(rec.a_ft);
+          const uint32_t vp = vtn + npush;
+          if (vp - vhn <= vmaskn) {
+            vrn[vp & vmaskn] = v;
+            npush++;
+            vlast = v;
+          } else {
+            lflags |= kFlagCap;  // bounded by construction; guards the ring
+          }
+          bpush += (int32_t)(le + rk);
+          dM += (int32_t)(le + rk);
+        }
+        rc[node].L = 0;  // no longer in the segment
       }
-      if (group_bits<G>(node != kNil || nbuf != 0) == 0) break;
+      node = nxt;
     }
+    // segments in order
+    lat_sum = add_in_order<G>(lat_sum, part, ballot(part != 0.0));
     {
       const uint32_t np = seg_prev<G>(npush);
       const int32_t bp = (int32_t)seg_prev<G>((uint32_t)bpush);

@@ -883,7 +883,7 @@ int advance_impl(const ws_job *jobs, int32_t n_jobs, const Layout &Lo, int64_t h
     B.lanes = Lo.lanes[pk];
     B.min_waves = kMinWavesLanes;
     B.any_trace = B.any_tv = B.any_caps = 0;
-    B.unit_n = pk == WS_WAIT ? 1 : 0;
+    B.unit_n = pk == WS_WAIT || pk == WS_NESTED_WAIT ? 1 : 0;
     for (int i = 0; i < n_jobs; ++i) {
       if (launch_kind(jobs[i]) != pk) continue;
       if (jobs[i].cfg->n_trace > 0) B.any_trace = 1;
@@ -892,6 +892,12 @@ int advance_impl(const ws_job *jobs, int32_t n_jobs, const Layout &Lo, int64_t h
       if (pk == WS_WAIT)
         for (int j = 0; j < jobs[i].cfg->m; ++j)
           if (jobs[i].pol->n[j] != 1) B.unit_n = 0;
+      if (pk == WS_NESTED_WAIT) {
+        for (int k = 0; k < jobs[i].pol->L; ++k)
+          if (jobs[i].pol->n[k] != 1) B.unit_n = 0;
+        // (that kernel keeps drawn lengths in 16 bits)
+        if (!jobs[i].cfg->out_len && jobs[i].cfg->out_cap > 65535) B.unit_n = 0;
+      }
     }
     if (launched > 0) sj.pending[sj.n_pending++] = ls;  // joined even if the launch fails
     hipError_t e = hipSuccess;
