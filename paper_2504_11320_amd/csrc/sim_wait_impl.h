@@ -448,7 +448,7 @@ sim_wait_kernel(KArgs A) {
     if (TV && trace) {
       in_order(live, INFINITY);
     } else {
-      for (;;) {
+      for (bool stuck = false;;) {
         // up to what every ring of the group knows
         double tm = group_min<G>(arr.te);
         Mask more = ballot(tm <= t_end) & inb;
@@ -460,6 +460,12 @@ sim_wait_kernel(KArgs A) {
         const uint32_t qt0 = qt, rp0 = arr.rp;
         const double pa0 = part_a;
         Mask run = ballot(arr.tn <= t_end) & ballot(arr.tn < tm) & inb;
+        if (run == 0 && more != 0 && stuck) {
+          // rings full of one instant (gaps below the clock's resolution)
+          in_order(live, INFINITY);
+          break;
+        }
+        stuck = run == 0;
         while (run != 0) {
           if (in(run)) {
             part_a += t_end - arr.tn;

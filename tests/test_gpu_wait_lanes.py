@@ -60,6 +60,21 @@ def test_full_queues():
     assert (g["flags"] & B.WS_FLAG_CAPACITY).sum() > 0
 
 
+def test_gaps_below_the_clock():
+    """Rates so high that gaps vanish beside the clock: rings of equal arrival
+    times, until the queue overflows."""
+    B = sim_module()
+    jobs = []
+    for m, n in ((1, 1), (3, 1), (3, 2)):
+        wl = W.Workload(prompt_len=[4, 9, 2][:m], lam=[1e12, 2e-6, 3e11][:m], d0=1e6, d1=1.0,
+                        C=400, policy="wait", n=[n] * m, out_len=[3, 5, 2][:m],
+                        hist_edges=W.default_edges(1e6, 32), record_capacity=1 << 12)
+        slow = dataclasses.replace(wl, lam=[1e-7, 1e-6, 1e-7][:m])
+        jobs += [W.Job(wl, 3, W.ids(5)), W.Job(slow, 4, W.ids(5))]
+    g, _ = check(B, jobs, 40, "gaps below the clock")
+    assert (g["flags"] & B.WS_FLAG_CAPACITY).sum() > 0
+
+
 def test_more_replicas_than_a_launch_spreads():
     """32 jobs of 512 and of 37 replicas: wavefronts full of groups, and the
     narrow ones of a small launch, give the same replicas the same bits."""
