@@ -50,17 +50,17 @@ CSRC = os.path.join(ROOT, "paper_2504_11320_amd", "csrc")
 # to the kernel it was measured on).
 _WAIT_SRCS = ("sim_wait_impl.h", "sim_arrivals.h", "sim_lanes.h", "sim_wait.hip", "sim_common.h")
 PROFILES = {
-    "wait-llama": ("sim_known_wait_3type_32x1024x1e5", _WAIT_SRCS),
-    "wait-cyclic": ("sim_known_wait_tv_3type_cyclic_32x1024x1e5",
+    "wait-llama": ("sim_wait_3type_32x1024x1e5", _WAIT_SRCS),
+    "wait-cyclic": ("sim_wait_tv_3type_cyclic_32x1024x1e5",
                     ("sim_wait_impl.h", "sim_arrivals.h", "sim_lanes.h", "sim_wait_tv.hip",
                      "sim_common.h")),
-    "nested-geometric": ("sim_nested_3type_geometric_32x1024x1e5",
+    "nested-geometric": ("sim_nested_unit_3type_geometric_32x1024x1e5",
                          ("sim_nested_unit_impl.h", "sim_arrivals.h", "sim_lanes.h",
                           "sim_nested_unit.hip", "sim_common.h")),
-    "nested-heavytail": ("sim_nested_10type_lognormal_8192x1e6",
+    "nested-heavytail": ("sim_nested_unit_10type_lognormal_8192x1e6",
                          ("sim_nested_unit_impl.h", "sim_arrivals.h", "sim_lanes.h",
                           "sim_nested_unit.hip", "sim_common.h")),
-    "fcfs-chunked": ("sim_known_fcfs_3type_chunk512_32x1024x1e5",
+    "fcfs-chunked": ("sim_fcfs_3type_chunk512_32x1024x1e5",
                      ("sim_fcfs_impl.h", "sim_arrivals.h", "sim_lanes.h", "sim_fcfs.hip", "sim_common.h")),
 }
 

@@ -32,8 +32,10 @@ HIPCC_FLAGS = [
 
 
 # Instruction-scheduling strategy per translation unit (LLVM's AMDGPU
-# scheduler), as measured: the known-length WAIT and the Nested WAIT kernels
-# gain from the ILP-maximising one, the FCFS kernels lose.
+# scheduler), as measured: the ILP-maximising one against the default is worth
+# 1 % on the Nested WAIT kernel for unit thresholds (41.9 against 42.4 ms on the
+# heavy-tailed mix), nothing on WAIT (14.52 against 14.47 ms) and costs FCFS 4 %
+# (11.87 against 11.44 ms on the chunked mix).
 SCHED_FLAGS = {
     "sim_wait.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"],
     "sim_wait_tv.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"],
