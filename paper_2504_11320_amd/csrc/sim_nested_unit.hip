@@ -5,6 +5,9 @@
 namespace wsim {
 
 hipError_t launch_nested_unit(int max_m, int max_seg, const KArgs &A, hipStream_t s) {
+  // what the kernel does not read would be left out without an error
+  if (!A.unit_n || A.any_trace || A.any_tv || A.any_caps || A.btrace != nullptr)
+    return hipErrorInvalidValue;
   const int G = nested_group_width(max_m, max_seg);
   // the host's replica list holds 64 / G replicas per wavefront
   if (A.lanes != 64 / G || A.n_list % 64 != 0) return hipErrorInvalidValue;

@@ -1,8 +1,9 @@
 """The Nested WAIT kernel for unit thresholds at the sizes where its branches
 change: every lane-group width, segments of one processing stage, one segment,
 short and long calendars, known and drawn lengths, tight memory (evictions of
-every kind), full queues; and workspaces that pass between it and the general
-kernel.  Every field against the oracle."""
+every kind), full queues; workspaces that pass between it and the general
+kernel; and arrival lists, which launches with unit thresholds replay in the
+general kernel.  Every field against the oracle."""
 import numpy as np
 import pytest
 
@@ -65,3 +66,41 @@ def test_between_kernels():
             else:
                 sim.advance_traced(300, 4, resume=i > 0)
         compare(sim.results(), want, order)
+
+
+def _list_job(rng, m, ends, replicas, known, lam=0.0, arrivals=400):
+    """A fixed arrival list (some arrivals at one instant) over m types."""
+    top = ends[-1]
+    lp = [int(x) for x in rng.integers(1, top, m - 1)] + [top]
+    times = np.sort(rng.choice(np.linspace(0.0, 900.0, 251), arrivals))
+    types = rng.integers(0, m, arrivals)
+    l = [int(x) for x in rng.integers(1, 60, m)]
+    wl = W.trace_workload("nested", l, lp if known else None, 1.0, 0.01,
+                          int((max(l) + top) * rng.uniform(1.0, 4.0)) + 1, [1] * len(ends),
+                          times, types, lengths=None if known else rng.integers(1, top + 1, arrivals),
+                          seg_end=list(ends), out_cap=0 if known else top,
+                          record_capacity=1 << 10)
+    wl.lam = [lam] * m
+    return W.Job(wl, int(rng.integers(0, 2**63)), W.ids(replicas))
+
+
+@pytest.mark.parametrize("m", [1, 3, 7, 20])
+def test_arrival_lists(m):
+    """Unit thresholds and an arrival list, with known and per-request lengths,
+    rates of zero and rates that the list replaces: every arrival of the list
+    is taken, alone and beside a job that draws its arrivals, and a traced
+    advance gives the same."""
+    B = sim_module()
+    rng = np.random.default_rng(70 + m)
+    lists = [_list_job(rng, m, ENDS[e], r, kn, lam) for e in (1, 4) for r, kn in ((2, True), (5, False))
+             for lam in (0.0, 0.3)]
+    for jobs, ctx in ((lists, "lists"), (lists[:3] + [_job(rng, m, ENDS[4], 9, 2.0)], "lists and draws")):
+        g, _ = check(B, jobs, 2500, f"unit Nested WAIT, {m} types, {ctx}")
+        # (tight memory can evict a replica's every prompt before its end)
+        assert g["completions"].sum() > 0 and (g["arrivals"] > 0).all()
+        sim = B.Simulation(jobs)
+        sim.prepare()
+        sim.advance_traced(2500, 1)
+        traced = sim.results()
+        for k in g:
+            assert np.array_equal(g[k], traced[k]), k
