@@ -200,6 +200,83 @@ struct Arrivals {
   }
 };
 
+// A fixed arrival list, read ahead into LDS by the lanes of each group.  A load
+// per arrival would be waited for together with every store before it: WAIT, one
+// type, 512 replicas x 400 batches of 2.5 arrivals took 1.48 ms with one and takes
+// 1.09; FCFS, three types, 32,768 replicas 2.83 and 1.41 (there also because two
+// wavefronts per SIMD then fit).
+template <int G>
+struct ListArrivals {
+  static constexpr uint32_t D = 8 * G;  // entries of a group
+  double *at;                           // this group's part of LDS, [D] each
+  uint32_t *aj;
+  const double *time;
+  const int32_t *type;
+  int64_t n;
+  int64_t end;   // the next entry to load
+  uint32_t pos;  // the next arrival (low word of its index): tn, jn (at the
+                 // end of the list +inf), the one after it: tn2, jn2
+  double tn = INFINITY, tn2 = INFINITY;
+  int32_t jn = 0, jn2 = 0;
+
+  // at_, aj_: 512 entries of the wavefront's LDS.
+  __device__ __forceinline__ ListArrivals(double *at_, uint32_t *aj_, const double *time_,
+                                          const int32_t *type_, int64_t n_, int64_t pos_)
+      : at(at_ + (threadIdx.x / G) * D), aj(aj_ + (threadIdx.x / G) * D), time(time_), type(type_),
+        n(n_), end(pos_), pos((uint32_t)pos_) {}
+  __device__ __forceinline__ uint32_t ahead() const { return (uint32_t)end - pos; }
+  __device__ __forceinline__ int64_t index() const { return end - (int64_t)ahead(); }
+  __device__ __forceinline__ void next2() {
+    tn2 = at[(pos + 1u) & (D - 1u)];
+    jn2 = (int32_t)aj[(pos + 1u) & (D - 1u)];
+  }
+  // Every group of `live` with half of its part free loads the next entries,
+  // four per lane (each lane of the wavefront takes part).
+  __device__ __forceinline__ void fill(Mask live) {
+    wave_lds_sync();
+    if (in(ballot(ahead() <= D / 2) & live)) {
+      const uint32_t gl = threadIdx.x & (G - 1);
+      double t[4];
+      int32_t j[4];
+#pragma unroll
+      for (uint32_t i = 0; i < 4; ++i) {
+        const int64_t e = end + (int64_t)(gl + i * G);
+        const bool left = e < n;
+        t[i] = left ? time[e] : INFINITY;
+        j[i] = left ? type[e] : 0;
+      }
+#pragma unroll
+      for (uint32_t i = 0; i < 4; ++i) {
+        const uint32_t x = ((uint32_t)end + gl + i * G) & (D - 1u);
+        at[x] = t[i];
+        aj[x] = (uint32_t)j[i];
+      }
+      end += 4 * G;
+    }
+    wave_lds_sync();
+  }
+  __device__ __forceinline__ void start(Mask live) {
+    fill(live);
+    if (in(live)) {
+      tn = at[pos & (D - 1u)];
+      jn = (int32_t)aj[pos & (D - 1u)];
+      next2();
+    }
+  }
+  // The next arrival of the groups of `go` has been taken (each lane of the
+  // wavefront takes part; `live`: the groups still running).
+  __device__ __forceinline__ void advance(Mask go, Mask live) {
+    if ((ballot(ahead() < 3u) & go) != 0) fill(live);
+    if (in(go)) {
+      pos++;
+      tn = tn2;
+      jn = jn2;
+      __builtin_amdgcn_sched_barrier(0);  // (as in Arrivals::advance)
+      next2();
+    }
+  }
+};
+
 // Stage the rate profile of job J in LDS (every lane of the wavefront).
 template <int G, int NP>
 __device__ __forceinline__ void stage_profile(const KArgs &A, const JobDev &J,

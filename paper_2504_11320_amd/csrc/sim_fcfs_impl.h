@@ -45,15 +45,17 @@ struct QLds {
   int32_t j, l;
 };
 
-// TV: the general instantiation (time-varying rates, arrival lists, per-batch
-// trace).
-template <int G, bool TV>
+// TV: the general instantiation (time-varying rates, per-batch trace); LIST:
+// arrival lists too.
+template <int G, bool TV, bool LIST>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2)))
 sim_fcfs_kernel(KArgs A) {
   constexpr int RING = 512;   // arrival times drawn ahead, of a wavefront
   constexpr int QRING = 256;  // queue records in LDS, of a wavefront
   constexpr int NL = G >= 4 ? 1 : 4 / G;  // queue records a lane loads at a time
-  constexpr int WB = 8;  // the last records pushed on each deque, for LIFO evictions
+  // the last records pushed on each deque, for LIFO evictions (with lists as
+  // many as leave room for two wavefronts per SIMD with 3 to 8 types)
+  constexpr int WB = LIST ? 4 : 8;
   constexpr int KC = 8;  // records at the front of the deque loaded at the launch
   __shared__ typename Arrivals<G, TV, RING>::Lds s_arr;
   __shared__ DRec s_win[WB][64];
@@ -84,7 +86,7 @@ sim_fcfs_kernel(KArgs A) {
   const int m = J.m;
   const int n_hist = J.n_hist;
   const int P = TV ? J.n_rate : 0;
-  const bool trace = TV && J.n_trace > 0;
+  const bool trace = LIST && J.n_trace > 0;
   const bool is_t = gl < m;
   {
     const double *edges_g = (const double *)(A.ws + J.off_edges);
@@ -103,9 +105,6 @@ sim_fcfs_kernel(KArgs A) {
   const int32_t C = (int32_t)J.C;  // <= 2^30
   const int32_t cap_adm = (int32_t)(J.C - J.reserve_tok);
   const int32_t chunk = J.chunk;  // prefill tokens per iteration (0: whole prefills)
-  const int64_t n_trace = J.n_trace;
-  const double *tr_time = (const double *)(A.ws + J.off_tr_time);
-  const int32_t *tr_type = (const int32_t *)(A.ws + J.off_tr_type);
   const uint32_t qmask = (1u << J.qcap_log2) - 1u;
   const uint32_t rec_cap = (uint32_t)J.rec_cap;
   uint32_t *hist = (uint32_t *)(A.ws + A.off_hist) + r * (int64_t)A.hist_stride;
@@ -214,6 +213,9 @@ sim_fcfs_kernel(KArgs A) {
     arr.start(live);
     if (draws && !A.resume && arr.limited()) flags |= kFlagThin;
   }
+  ListArrivals<G> lst(s_arr.at, s_arr.ak, (const double *)(A.ws + J.off_tr_time),
+                      (const int32_t *)(A.ws + J.off_tr_type), J.n_trace, tridx);
+  if (LIST && trace) lst.start(live);
 
   // ---- the queue ----------------------------------------------------------
   // Records qh .. qc-1 are in LDS (a power of two of them at most, shared out
@@ -279,12 +281,10 @@ sim_fcfs_kernel(KArgs A) {
   // ---- arrivals -------------------------------------------------------------
   // The group's next arrival and the lanes of its type(s).
   auto peek = [&](Mask &mine) __attribute__((always_inline)) -> double {
-    if constexpr (TV) {
+    if constexpr (LIST) {
       if (trace) {
-        const bool left = tridx < n_trace;
-        const double ta = left ? tr_time[tridx] : INFINITY;
-        mine = ballot(gl == tr_type[left ? tridx : 0]) & ballot(left);
-        return ta;
+        mine = ballot(gl == lst.jn);
+        return lst.tn;
       }
     }
     const double ta = group_min<G>(arr.tn);
@@ -299,16 +299,16 @@ sim_fcfs_kernel(KArgs A) {
     if constexpr (G > 1) {
       if (__popcll(me) * G != __popcll(go)) me = group_lowest<G>(me);
     }
-    if constexpr (TV) {
-      if (trace && in(go)) tridx++;
-    }
     // rare: the ring of arrival times runs low, or the queue is full
     const Mask low = arr.low();
     const Mask full = ballot(qt - qh >= rec_cap);
     more &= ~(go & full);
     if ((me & low) != 0) arr.refill(live);
     push_q(go, me, ta);
-    if (in(me)) {
+    if (LIST && trace) {
+      if (in(me)) arr.rp++;
+      lst.advance(go, live);
+    } else if (in(me)) {
       arr.advance();
       if (arr.limited()) flags |= kFlagThin;
     }
@@ -464,15 +464,30 @@ sim_fcfs_kernel(KArgs A) {
 
     // ---- arrivals during the batch ----------------------------------------
     Mask inb = live;
-    for (;;) {
-      Mask mine;
-      const double ta = peek(mine);
-      const Mask go = ballot(ta <= t_end) & inb;
-      if (go == 0) break;
-      const double w = in(go) ? t_end - ta : 0.0;  // (areas are never -0)
-      lat_area += w;
-      ttft_area += w;
-      take(go, mine, ta, inb);
+    if (LIST && trace) {
+      for (;;) {
+        const Mask go = ballot(lst.tn <= t_end) & inb;
+        if (go == 0) break;
+        const double w = in(go) ? t_end - lst.tn : 0.0;  // (areas are never -0)
+        lat_area += w;
+        ttft_area += w;
+        const Mask me = go & ballot(gl == lst.jn);
+        inb &= ~ballot(qt - qh >= rec_cap);
+        push_q(go, me, lst.tn);
+        if (in(me)) arr.rp++;
+        lst.advance(go, live);
+      }
+    } else {
+      for (;;) {
+        Mask mine;
+        const double ta = peek(mine);
+        const Mask go = ballot(ta <= t_end) & inb;
+        if (go == 0) break;
+        const double w = in(go) ? t_end - ta : 0.0;
+        lat_area += w;
+        ttft_area += w;
+        take(go, mine, ta, inb);
+      }
     }
     if (in(live)) {
       lat_area += (double)N0 * tau;
@@ -668,7 +683,7 @@ sim_fcfs_kernel(KArgs A) {
     put_i(A, S_N, r, N);
     put_i(A, S_U, r, U);
     put_i(A, S_MRES, r, Mres);
-    put_i(A, S_TRIDX, r, tridx);
+    put_i(A, S_TRIDX, r, trace ? lst.index() : tridx);
     put_i(A, S_FLAGS, r, (int64_t)flags);
     put_i(A, S_QH, r, qh);
     put_i(A, S_QT, r, qt);
@@ -683,22 +698,22 @@ sim_fcfs_kernel(KArgs A) {
   }
 }
 
-template <int G, bool TV>
+template <int G, bool TV, bool LIST>
 hipError_t launch_fcfs_g(KArgs A, hipStream_t s) {
   // replicas per wavefront: what the group width allows, within the list's
   A.nr = 64 / G < A.lanes ? 64 / G : A.lanes;
   if (A.n_list % 64 != 0 || A.lanes % A.nr != 0) return hipErrorInvalidValue;
   while (A.nr > 1 && (int64_t)(A.n_list / 64) * (A.lanes / A.nr) < A.min_waves) A.nr /= 2;
-  return launch_checked(sim_fcfs_kernel<G, TV>, dim3((A.n_list / 64) * (A.lanes / A.nr)), s, A);
+  return launch_checked(sim_fcfs_kernel<G, TV, LIST>, dim3((A.n_list / 64) * (A.lanes / A.nr)), s, A);
 }
 
-template <bool TV>
+template <bool TV, bool LIST>
 hipError_t launch_fcfs_k(int max_m, const KArgs &A, hipStream_t s) {
-  if (max_m <= 1) return launch_fcfs_g<1, TV>(A, s);
-  if (max_m <= 2) return launch_fcfs_g<2, TV>(A, s);
-  if (max_m <= 4) return launch_fcfs_g<4, TV>(A, s);
-  if (max_m <= 8) return launch_fcfs_g<8, TV>(A, s);
-  if (max_m <= 16) return launch_fcfs_g<16, TV>(A, s);
+  if (max_m <= 1) return launch_fcfs_g<1, TV, LIST>(A, s);
+  if (max_m <= 2) return launch_fcfs_g<2, TV, LIST>(A, s);
+  if (max_m <= 4) return launch_fcfs_g<4, TV, LIST>(A, s);
+  if (max_m <= 8) return launch_fcfs_g<8, TV, LIST>(A, s);
+  if (max_m <= 16) return launch_fcfs_g<16, TV, LIST>(A, s);
   return hipErrorInvalidValue;  // more types run in the kernel for drawn lengths
 }
 

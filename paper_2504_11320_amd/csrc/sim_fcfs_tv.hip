@@ -5,7 +5,8 @@
 namespace wsim {
 
 hipError_t launch_fcfs_tv(int max_m, const KArgs &A, hipStream_t s) {
-  return launch_fcfs_k<true>(max_m, A, s);
+  if (A.any_trace) return launch_fcfs_k<true, true>(max_m, A, s);
+  return launch_fcfs_k<true, false>(max_m, A, s);
 }
 
 }  // namespace wsim

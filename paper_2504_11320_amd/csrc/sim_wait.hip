@@ -9,8 +9,8 @@ hipError_t launch_wait(int max_m, const KArgs &A, hipStream_t s) {
   // run in the general instantiation
   if (A.any_trace || A.any_tv || A.btrace != nullptr || A.any_caps)
     return launch_wait_tv(max_m, A, s);
-  if (A.unit_n) return launch_wait_k<false, true>(max_m, A, s);
-  return launch_wait_k<false, false>(max_m, A, s);
+  if (A.unit_n) return launch_wait_k<false, true, false>(max_m, A, s);
+  return launch_wait_k<false, false, false>(max_m, A, s);
 }
 
 }  // namespace wsim

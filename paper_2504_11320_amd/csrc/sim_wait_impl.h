@@ -46,10 +46,10 @@
 namespace wsim {
 namespace {
 
-// TV: the general instantiation (time-varying rates, arrival lists, per-stage
-// caps, per-batch trace).  ONE: every threshold is 1 (at most one admission
-// and one completion per type and batch).
-template <int G, bool TV, bool ONE>
+// TV: the general instantiation (time-varying rates, per-stage caps, per-batch
+// trace); LIST: arrival lists too.  ONE: every threshold is 1 (at most one
+// admission and one completion per type and batch).
+template <int G, bool TV, bool ONE, bool LIST>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2)))
 sim_wait_kernel(KArgs A) {
   // Arrival times are drawn ahead of use by the whole wavefront into a ring
@@ -59,9 +59,11 @@ sim_wait_kernel(KArgs A) {
   constexpr int WB = 8;
   // records loaded at the launch for use at the completion: a cohort's queue
   // records (a larger cohort enters the deque at the launch) and the records
-  // at the front of the deque
-  constexpr int KQ = ONE ? 1 : 16;
-  constexpr int KC = ONE ? 2 : 8;
+  // at the front of the deque (fewer with lists, whose state would push 16 and
+  // 8 into scratch memory: 124 bytes a lane)
+  constexpr int KQ = ONE ? 1 : LIST ? 4 : 16;
+  constexpr int VQ = LIST ? 3 : 5;  // of a cohort's records after the first, at a time
+  constexpr int KC = ONE || LIST ? 2 : 8;
   __shared__ typename Arrivals<G, TV, RING>::Lds s_arr;
   __shared__ DRec s_win[WB][64];
   __shared__ double s_edges[WS_MAX_HIST_EDGES + 1];
@@ -89,7 +91,7 @@ sim_wait_kernel(KArgs A) {
   const int m = J.m;
   const int n_hist = J.n_hist;
   const int P = TV ? J.n_rate : 0;
-  const bool trace = TV && J.n_trace > 0;
+  const bool trace = LIST && J.n_trace > 0;
   const bool is_t = gl < m;
   {
     const double *edges_g = (const double *)(A.ws + J.off_edges);
@@ -106,9 +108,6 @@ sim_wait_kernel(KArgs A) {
   const double d0 = J.d0, d1 = J.d1;
   const int32_t C = (int32_t)J.C;  // <= 2^30
   const bool nowait = J.nowait != 0;
-  const int64_t n_trace = J.n_trace;
-  const double *tr_time = (const double *)(A.ws + J.off_tr_time);
-  const int32_t *tr_type = (const int32_t *)(A.ws + J.off_tr_type);
   const uint32_t qmask = (1u << J.qcap_log2) - 1u;
   const uint32_t rec_cap = (uint32_t)J.rec_cap;
   uint32_t *hist = (uint32_t *)(A.ws + A.off_hist) + r * (int64_t)A.hist_stride;
@@ -225,16 +224,17 @@ sim_wait_kernel(KArgs A) {
     arr.start(live);
     if (draws && !A.resume && arr.limited()) flags |= kFlagThin;
   }
+  ListArrivals<G> lst(s_arr.at, s_arr.ak, (const double *)(A.ws + J.off_tr_time),
+                      (const int32_t *)(A.ws + J.off_tr_type), J.n_trace, tridx);
+  if (LIST && trace) lst.start(live);
 
   // ---- arrivals ---------------------------------------------------------------
   // The group's next arrival and the lanes of its type(s).
   auto peek = [&](Mask &mine) __attribute__((always_inline)) -> double {
-    if constexpr (TV) {
+    if constexpr (LIST) {
       if (trace) {
-        const bool left = tridx < n_trace;
-        const double ta = left ? tr_time[tridx] : INFINITY;
-        mine = ballot(gl == tr_type[left ? tridx : 0]) & ballot(left);
-        return ta;
+        mine = ballot(gl == lst.jn);
+        return lst.tn;
       }
     }
     const double ta = group_min<G>(arr.tn);
@@ -250,9 +250,6 @@ sim_wait_kernel(KArgs A) {
     if constexpr (G > 1) {
       if (__popcll(me) * G != __popcll(go)) me = group_lowest<G>(me);
     }
-    if constexpr (TV) {
-      if (trace && in(go)) tridx++;
-    }
     // rare: the ring of arrival times runs low, or the queue is full
     const Mask low = arr.low();
     const Mask full = ballot(qt - qh >= rec_cap);
@@ -264,6 +261,11 @@ sim_wait_kernel(KArgs A) {
     if (in(me)) {
       qr[qt & qmask] = ta;  // a full queue is not read again
       qt++;
+    }
+    if (LIST && trace) {
+      if (in(me)) arr.rp++;
+      lst.advance(go, live);
+    } else if (in(me)) {
       arr.advance();
       if (arr.limited()) flags |= kFlagThin;
     }
@@ -409,10 +411,10 @@ sim_wait_kernel(KArgs A) {
     if (in(adm)) qa[0] = qr[qh & qmask];
     if constexpr (!ONE) {
 #pragma unroll
-      for (int v = 1; v < KQ; v += 5) {
+      for (int v = 1; v < KQ; v += VQ) {
         if (ballot(nd > (uint32_t)v) != 0) {
 #pragma unroll
-          for (int u = v; u < v + 5; ++u) qa[u] = qr[(qh + (uint32_t)u) & qmask];
+          for (int u = v; u < v + VQ; ++u) qa[u] = qr[(qh + (uint32_t)u) & qmask];
         }
       }
     }
@@ -445,8 +447,24 @@ sim_wait_kernel(KArgs A) {
         part_a += in(me) ? t_end - ta : 0.0;
       }
     };
-    if (TV && trace) {
-      in_order(live, INFINITY);
+    if (LIST && trace) {  // the list's next arrival, whichever its type
+      for (;;) {
+        const Mask go = ballot(lst.tn <= t_end) & inb;
+        if (go == 0) break;
+        const Mask me = go & ballot(gl == lst.jn);
+        if (in(me)) {
+          part_a += t_end - lst.tn;
+          qr[qt & qmask] = lst.tn;
+          qt++;
+          arr.rp++;
+        }
+        const Mask full = ballot(qt - qh > rec_cap) & me;
+        if (full != 0) {
+          if (in(full)) flags |= kFlagCap;
+          inb &= ~group_spread<G>(full);
+        }
+        lst.advance(go, live);
+      }
     } else {
       for (bool stuck = false;;) {
         // up to what every ring of the group knows
@@ -738,7 +756,7 @@ sim_wait_kernel(KArgs A) {
     put_i(A, S_N, r, N);
     put_i(A, S_U, r, U);
     put_i(A, S_MRES, r, Mres);
-    put_i(A, S_TRIDX, r, tridx);
+    put_i(A, S_TRIDX, r, trace ? lst.index() : tridx);
     put_i(A, S_FLAGS, r, (int64_t)flags);
   }
   if (is_t) {
@@ -754,24 +772,24 @@ sim_wait_kernel(KArgs A) {
   }
 }
 
-template <int G, bool TV, bool ONE>
+template <int G, bool TV, bool ONE, bool LIST>
 hipError_t launch_wait_g(KArgs A, hipStream_t s) {
   // replicas per wavefront: what the group width allows, within the list's
   A.nr = 64 / G < A.lanes ? 64 / G : A.lanes;
   if (A.n_list % 64 != 0 || A.lanes % A.nr != 0) return hipErrorInvalidValue;
   while (A.nr > 1 && (int64_t)(A.n_list / 64) * (A.lanes / A.nr) < A.min_waves) A.nr /= 2;
-  return launch_checked(sim_wait_kernel<G, TV, ONE>, dim3((A.n_list / 64) * (A.lanes / A.nr)), s, A);
+  return launch_checked(sim_wait_kernel<G, TV, ONE, LIST>, dim3((A.n_list / 64) * (A.lanes / A.nr)), s, A);
 }
 
-template <bool TV, bool ONE>
+template <bool TV, bool ONE, bool LIST>
 hipError_t launch_wait_k(int max_m, const KArgs &A, hipStream_t s) {
-  if (max_m <= 1) return launch_wait_g<1, TV, ONE>(A, s);
-  if (max_m <= 2) return launch_wait_g<2, TV, ONE>(A, s);
-  if (max_m <= 4) return launch_wait_g<4, TV, ONE>(A, s);
-  if (max_m <= 8) return launch_wait_g<8, TV, ONE>(A, s);
-  if (max_m <= 16) return launch_wait_g<16, TV, ONE>(A, s);
-  if (max_m <= 32) return launch_wait_g<32, TV, ONE>(A, s);
-  if (max_m <= 64) return launch_wait_g<64, TV, ONE>(A, s);
+  if (max_m <= 1) return launch_wait_g<1, TV, ONE, LIST>(A, s);
+  if (max_m <= 2) return launch_wait_g<2, TV, ONE, LIST>(A, s);
+  if (max_m <= 4) return launch_wait_g<4, TV, ONE, LIST>(A, s);
+  if (max_m <= 8) return launch_wait_g<8, TV, ONE, LIST>(A, s);
+  if (max_m <= 16) return launch_wait_g<16, TV, ONE, LIST>(A, s);
+  if (max_m <= 32) return launch_wait_g<32, TV, ONE, LIST>(A, s);
+  if (max_m <= 64) return launch_wait_g<64, TV, ONE, LIST>(A, s);
   return hipErrorInvalidValue;  // the host admits at most WS_MAX_TYPES types
 }
 

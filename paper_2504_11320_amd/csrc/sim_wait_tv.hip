@@ -6,7 +6,8 @@
 namespace wsim {
 
 hipError_t launch_wait_tv(int max_m, const KArgs &A, hipStream_t s) {
-  return launch_wait_k<true, false>(max_m, A, s);
+  if (A.any_trace) return launch_wait_k<true, false, true>(max_m, A, s);
+  return launch_wait_k<true, false, false>(max_m, A, s);
 }
 
 }  // namespace wsim

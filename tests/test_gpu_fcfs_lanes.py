@@ -2,12 +2,13 @@
 at the sizes where its branches change: the queue's front in LDS (short and
 long queues, few and many replicas per wavefront, admissions past what LDS
 holds), cohorts around the 8 records loaded ahead, chunked prefill, full
-queues; every field against the oracle."""
+queues, arrival lists of lengths around what is read ahead; every field against the oracle."""
 import numpy as np
 import pytest
 
 import workloads as W
 from tests.gpu_util import check, sim_module
+from tests.test_gpu_wait_lanes import list_jobs
 
 pytestmark = pytest.mark.gpu
 
@@ -50,3 +51,25 @@ def test_full_queues():
             for chunk in (0, 8)]
     g, _ = check(B, jobs, 400, "FCFS full queues")
     assert (g["flags"] & B.WS_FLAG_CAPACITY).sum() > 0
+
+
+@pytest.mark.parametrize("m", [1, 2, 3, 5, 9, 16])
+def test_arrival_lists(m):
+    B = sim_module()
+    rng = np.random.default_rng(80 + m)
+    jobs = list_jobs(rng, "fcfs", m)
+    for j in jobs[::2]:
+        j.wl.chunk = 13
+    g, _ = check(B, jobs, 900, f"FCFS, lists, {m} types")
+    assert (g["flags"] & B.WS_FLAG_CAPACITY).sum() > 0
+    # a list continued in its middle; lists beside drawn arrivals and rate profiles
+    sim = B.Simulation(jobs)
+    for i, h in enumerate((3, 90, 807)):
+        sim.advance(h, resume=i > 0)
+    two = sim.results()
+    for k in g:
+        assert np.array_equal(g[k], two[k]), k
+    rt, rf = W.diurnal_profile(m, 900.0, points=9)
+    tv = _job(rng, m, 6, 1.0)
+    jobs = jobs[3:7] + [_job(rng, m, 9, 1.0), W.Job(W.with_profile(tv.wl, rt, rf), 5, W.ids(6))]
+    check(B, jobs, 400, f"FCFS, lists beside draws, {m} types")

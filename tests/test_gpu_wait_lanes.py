@@ -1,8 +1,8 @@
 """The WAIT kernel's lane groups (one lane per type, groups of 1 to 64 lanes)
 at the sizes where its branches change: cohorts around the 16 records loaded
 ahead and completions around the 8, one type to more than a 32-lane group,
-few and many replicas per wavefront, full queues, simultaneous arrivals;
-every field against the oracle (fp64 sums within the parity bound: the sums
+few and many replicas per wavefront, full queues, simultaneous arrivals, arrival
+lists of lengths around what is read ahead; every field against the oracle (fp64 sums within the parity bound: the sums
 per type and batch are taken type by type)."""
 import dataclasses
 
@@ -86,3 +86,42 @@ def test_more_replicas_than_a_launch_spreads():
     idx = np.concatenate([1200 * k + np.arange(37) for k in range(32)])
     for k in wide:
         assert np.array_equal(wide[k][idx], thin[k]), k
+
+
+def list_jobs(rng, policy, m, cap=1 << 9):
+    """Arrival lists over m types, several arrivals to an instant: of no more
+    entries than a few, around the 8 per lane that are read ahead, long ones;
+    a queue that overflows."""
+    jobs = []
+    for total in (1, 3, 4, 5, 8 * m - 1, 8 * m, 8 * m + 1, 64 * m + 3, 1500):
+        span = total * (0.05 if total == 1500 else 4.0)
+        times = np.sort(rng.choice(np.linspace(0.0, span, 2 * total + 1), total))
+        l = [int(x) for x in rng.integers(1, 40, m)]
+        lp = [int(x) for x in rng.integers(1, 12, m)]
+        n = [int(x) for x in rng.integers(1, 7, m)]
+        wl = W.trace_workload(policy, l, lp, 1.0, 0.005, int((max(l) + 12) * rng.uniform(1.5, 12.0)),
+                              [] if policy == "fcfs" else n, times, rng.integers(0, m, total),
+                              record_capacity=16 if total == 1500 else cap)
+        jobs.append(W.Job(wl, 0, W.ids(int(rng.integers(1, 70)))))
+    return jobs
+
+
+@pytest.mark.parametrize("m", [1, 2, 3, 5, 9, 17, 33])
+def test_arrival_lists(m):
+    B = sim_module()
+    rng = np.random.default_rng(60 + m)
+    jobs = list_jobs(rng, "wait", m) + list_jobs(rng, "wait-nowait", m)
+    g, _ = check(B, jobs, 700, f"WAIT, lists, {m} types")
+    assert (g["flags"] & B.WS_FLAG_CAPACITY).sum() > 0
+    # a list continued in its middle; lists beside drawn arrivals and rate profiles
+    sim = B.Simulation(jobs)
+    for i, h in enumerate((3, 90, 607)):
+        sim.advance(h, resume=i > 0)
+    two = sim.results()
+    for k in g:
+        assert np.array_equal(g[k], two[k]), k
+    if m <= 16:
+        rt, rf = W.diurnal_profile(m, 900.0, points=9)
+        tv = _job(rng, m, 1, 3, "wait", 11)
+        jobs = jobs[3:7] + [_job(rng, m, 1, 3, "wait", 9), W.Job(W.with_profile(tv.wl, rt, rf), 5, W.ids(6))]
+        check(B, jobs, 400, f"WAIT, lists beside draws, {m} types")
