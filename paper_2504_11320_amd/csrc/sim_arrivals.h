@@ -37,8 +37,8 @@ struct Arrivals {
   double lam;
   bool tv;
   Mask draw_m;  // lanes that draw
-  // The pending arrival (tn) and the next (tn2) lead the ring of entries rp ..
-  // re-1, whose last is at te; kc is the next candidate to draw, tl the clock
+  // The pending arrival (tn) and the next (tn2, if it is known) lead the ring
+  // of entries rp .. re-1, whose last is at te; kc is the next candidate to draw, tl the clock
   // it starts from.
   double tn = INFINITY, tn2 = INFINITY, te = INFINITY, tl = 0.0;
   uint32_t rp = 0, re = 0, kc = 0;
@@ -74,8 +74,11 @@ struct Arrivals {
   // Every lane of `live` with room for gu draws asks for them and the
   // wavefront draws all of them together; then each asking lane turns its
   // gaps into arrival times (with a rate profile, its candidates into the
-  // kept ones).  Every lane of the wavefront takes part.
-  __device__ __forceinline__ void refill(Mask live) {
+  // kept ones).  Thinning may keep none of them, up to kThinMax in a row, so
+  // only the lanes of `need`, whose arrivals are about to be taken, go on until
+  // they hold `least`; the others' later arrivals may never be reached.  Every
+  // lane of the wavefront takes part.
+  __device__ __forceinline__ void refill(Mask live, Mask need, uint32_t least = 2u) {
     Mask again;
     do {
       Mask room = ballot(re - rp <= dm + 1u - gu) & live & draw_m;
@@ -155,21 +158,19 @@ struct Arrivals {
         tn2 = S.at[slot(rp + 1u, tx)];
       }
       wave_lds_sync();
-      // thinning may have kept too few: a lane needs the pending arrival, the
-      // next one and the one after it
       again = 0;
-      if constexpr (TV) again = ballot(re - rp < 3u) & ballot(!ended) & live & draw_m;
+      if constexpr (TV) again = ballot(re - rp < least) & ballot(!ended) & live & draw_m & need;
     } while (again != 0);
   }
-  // The pending arrival and the next one of the lanes of `live`, after the
-  // first refill.
+  // The pending arrivals of the lanes of `live`, after the first refill.
   __device__ __forceinline__ void start(Mask live) {
     wave_lds_sync();
-    refill(live);
+    refill(live, live, 1u);
     if (in(live & draw_m)) tn = S.at[slot(rp, tx)];
   }
-  // Lanes whose ring ends with the arrival after the next: to refill before
-  // they move on.
+  // Lanes whose ring ends with the next arrival: to refill before they move
+  // on (tn2 is then the pending one; what follows it in the ring, if it is
+  // not known yet, is set by the refill before it is used).
   __device__ __forceinline__ Mask low() const {
     Mask m = ballot(rp + 2u >= re) & draw_m;
     if constexpr (TV) m &= ~ballot(ended);

@@ -303,7 +303,7 @@ sim_fcfs_kernel(KArgs A) {
     const Mask low = arr.low();
     const Mask full = ballot(qt - qh >= rec_cap);
     more &= ~(go & full);
-    if ((me & low) != 0) arr.refill(live);
+    if ((me & low) != 0) arr.refill(live, me);
     push_q(go, me, ta);
     if (LIST && trace) {
       if (in(me)) arr.rp++;

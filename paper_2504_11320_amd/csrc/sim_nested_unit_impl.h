@@ -275,7 +275,7 @@ sim_nested_unit_kernel(KArgs A) {
     if (__popcll(me) * G != __popcll(go)) me = group_lowest<G>(me);
     const Mask low = arr.low();
     more &= ~(go & ballot(qt - qh >= rec_cap));
-    if ((me & low) != 0) arr.refill(live);
+    if ((me & low) != 0) arr.refill(live, me);
     const int32_t len = known ? lpk : (int32_t)s_arr.len[arr.slot(arr.rp, tx)];
     push_q(go, me, ta, tword, len);
     if (in(me)) arr.advance();

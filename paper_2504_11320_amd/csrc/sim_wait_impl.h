@@ -256,7 +256,7 @@ sim_wait_kernel(KArgs A) {
     if ((me & (low | full)) != 0) {
       if (in(me & full)) flags |= kFlagCap;
       more &= ~group_spread<G>(me & full);
-      if ((me & low) != 0) arr.refill(live);
+      if ((me & low) != 0) arr.refill(live, me);
     }
     if (in(me)) {
       qr[qt & qmask] = ta;  // a full queue is not read again
@@ -471,7 +471,7 @@ sim_wait_kernel(KArgs A) {
         double tm = group_min<G>(arr.te);
         Mask more = ballot(tm <= t_end) & inb;
         if (more != 0) {
-          arr.refill(live);
+          arr.refill(live, inb & ballot(arr.te <= t_end));
           tm = group_min<G>(arr.te);
           more = ballot(tm <= t_end) & inb;
         }

@@ -148,3 +148,47 @@ def test_random_profiles_with_chunked_fcfs(B):
         jobs.append(W.Job(W.with_profile(wl, rt, rf), int(rng.integers(0, 2**63)),
                           W.ids(int(rng.integers(1, 40)))))
     check(B, jobs, 600, "random profiles with chunked FCFS")
+
+
+def _tail_jobs(policy, tail):
+    """Type 1 arrives at full rate up to t = 1500 and at `tail` of it from 1501
+    on; a run of 100 batches ends before its arrivals do.  The replicas are
+    ones with a single arrival of it between t = 400 and 1500, after t = 1000."""
+    from oracle import oracle as O
+    wl = W.Workload(prompt_len=[4, 6], lam=[0.2, 0.002], d0=5.0, d1=0.001, C=400, policy=policy,
+                    n=[] if policy == "fcfs" else [1, 1], out_len=[3, 5],
+                    hist_edges=W.default_edges(5.0, 32), record_capacity=1 << 10)
+    rids = []
+    for rid in range(4000):
+        t = O.arrival_times(wl, 77, rid, 1, 16)[0]
+        if ((t > 400.0) & (t < 1500.0)).sum() == 1 and ((t > 1000.0) & (t < 1500.0)).sum() == 1:
+            rids.append(rid)
+        if len(rids) == 8:
+            break
+    prof = W.with_profile(wl, [0.0, 1500.0, 1501.0], [[1.0, 1.0, 1.0], [1.0, 1.0, tail]])
+    return [W.Job(prof, 77, np.array(rids, dtype=np.uint32))]
+
+
+@pytest.mark.parametrize("policy", ["wait", "fcfs"])
+def test_arrivals_beyond_the_run_are_not_searched_for(B, policy):
+    """A profile that goes on at a tiny rate rejects 2^20 candidates before the
+    type ends.  A run that stops before that takes about as long as with a rate
+    of zero there, where the first rejection ends the type (a factor of 5 for
+    noise; searched for, the candidates take a hundred times as long)."""
+    import torch
+    best = {}
+    for tail in (0.0, 1e-9):
+        jobs = _tail_jobs(policy, tail)
+        g, _ = check(B, jobs, 100, f"{policy}, tail {tail}")
+        assert g["t_end"].max() < 1000.0
+        sim = B.Simulation(jobs)
+        sim.prepare()
+        for _ in range(4):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            sim.advance(100)
+            b.record()
+            torch.cuda.synchronize()
+            best[tail] = min(best.get(tail, 1e9), a.elapsed_time(b))
+    print(f"[gpu] {policy}: {best}", flush=True)
+    assert best[1e-9] < 5.0 * best[0.0]
