@@ -475,7 +475,7 @@ sim_wait_kernel(KArgs A) {
           tm = group_min<G>(arr.te);
           more = ballot(tm <= t_end) & inb;
         }
-        const uint32_t qt0 = qt, rp0 = arr.rp;
+        const uint32_t qt0 = qt, rp0 = arr.rp, flags0 = flags;
         const double pa0 = part_a;
         Mask run = ballot(arr.tn <= t_end) & ballot(arr.tn < tm) & inb;
         if (run == 0 && more != 0 && stuck) {
@@ -500,6 +500,7 @@ sim_wait_kernel(KArgs A) {
           if (in(again)) {
             qt = qt0;
             part_a = pa0;
+            flags = flags0;
             if (draws) arr.rewind(rp0);
           }
           in_order(again, tm);

@@ -192,3 +192,22 @@ def test_arrivals_beyond_the_run_are_not_searched_for(B, policy):
             best[tail] = min(best.get(tail, 1e9), a.elapsed_time(b))
     print(f"[gpu] {policy}: {best}", flush=True)
     assert best[1e-9] < 5.0 * best[0.0]
+
+
+def test_limit_flag_of_an_arrival_not_taken(B):
+    """A queue overflows early in a batch, another type's last arrival before
+    it reaches the rejection limit lies later in that batch: it is not taken,
+    so the limit is not reported."""
+    from oracle import oracle as O
+    wl = W.Workload(prompt_len=[4, 6], lam=[1.5, 0.05], d0=100.0, d1=0.001, C=400, policy="wait",
+                    n=[1, 1], out_len=[3, 5], hist_edges=W.default_edges(5.0, 32),
+                    record_capacity=16)
+    rids = []
+    for rid in range(2000):
+        t = O.arrival_times(wl, 78, rid, 1, 8)[0]
+        if (t < 31.0).sum() == 1 and 22.0 < t[0] < 30.0:
+            rids.append(rid)
+    prof = W.with_profile(wl, [0.0, 30.0, 31.0], [[1.0, 1.0, 1.0], [1.0, 1.0, 1e-9]])
+    g, _ = check(B, [W.Job(prof, 78, np.array(rids[:24], dtype=np.uint32))], 3, "limit not reached")
+    assert ((g["flags"] & B.WS_FLAG_CAPACITY) != 0).all()
+    assert ((g["flags"] & B.WS_FLAG_THIN_LIMIT) == 0).any()
