@@ -718,6 +718,7 @@ sim_nested_unit_kernel(KArgs A) {
       node = rec.next;
       walk &= ballot(node != kNil);
     }
+    wave_lds_sync();  // s_vw: a survivor's record, read by the next segment's lane
     comp32 += ndone;
     lat_sum = add_in_order<G>(lat_sum, part, ballot(ndone != 0u));
     {
