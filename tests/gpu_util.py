@@ -2,7 +2,7 @@
 import numpy as np
 import pytest
 
-from tests.parity_util import compare
+from tests.parity_util import areas_ordered, compare
 
 
 def sim_module():
@@ -30,7 +30,7 @@ def check(B, jobs, horizon, ctx):
           f"horizon {horizon}", flush=True)
     g = B.run_batch(jobs, horizon)
     o = oracle_results(jobs, horizon)
-    st = compare(g, o, ctx)
+    st = compare(g, o, ctx, ordered=areas_ordered(jobs))
     print(f"[gpu] {ctx}: ok, fp64 bit-exact {st['f64_bit_exact']}/{st['f64_total']}",
           flush=True)
     return g, o

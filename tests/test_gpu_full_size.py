@@ -10,7 +10,7 @@ import numpy as np
 import pytest
 
 import workloads as W
-from tests.parity_util import compare
+from tests.parity_util import areas_ordered, compare
 
 pytestmark = [pytest.mark.gpu, pytest.mark.slow]
 
@@ -60,7 +60,7 @@ def _sampled(g, jobs, horizon, picks, ctx):
     idx = np.array([starts[ji] + pos for ji, pos in picks])
     gsub = {k: v[idx] for k, v in g.items()}
     gsub["hist"] = gsub["hist"][:, :width]
-    st = compare(gsub, o, ctx)
+    st = compare(gsub, o, ctx, ordered=areas_ordered(sub))
     print(f"[gpu] {ctx}: {len(picks)} sampled replicas ok, fp64 bit-exact "
           f"{st['f64_bit_exact']}/{st['f64_total']}", flush=True)
 

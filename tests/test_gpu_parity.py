@@ -1,9 +1,10 @@
 """GPU parity: the HIP path, called through the C ABI, against the oracle.
 
-Counts, admissions, evictions, flags and histograms must be identical; the
-fp64 time and latency accumulators must agree within 1e-12 relative (the
-two sides perform the same IEEE operations in the same order, so they are
-normally bit-identical).
+Counts, admissions, evictions, flags and histograms must be identical, and so
+must the fp64 accumulators that both sides sum in the same order (the clock,
+busy time and memory area; the areas of FCFS and Nested WAIT); the others agree
+within 1e-12 relative (the kernels sum a batch's terms per type or segment
+first).
 """
 import json
 import os
@@ -12,7 +13,7 @@ import numpy as np
 import pytest
 
 import workloads as W
-from tests.parity_util import compare
+from tests.parity_util import areas_ordered, compare
 
 pytestmark = pytest.mark.gpu
 
@@ -39,7 +40,7 @@ def _check(sim, jobs, horizon, ctx):
           f"horizon {horizon}", flush=True)
     g = sim.run_batch(jobs, horizon)
     o = _oracle(jobs, horizon)
-    st = compare(g, o, ctx)
+    st = compare(g, o, ctx, ordered=areas_ordered(jobs))
     print(f"[gpu] {ctx}: ok, fp64 bit-exact {st['f64_bit_exact']}/{st['f64_total']}",
           flush=True)
     return g, o
