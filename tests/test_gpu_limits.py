@@ -1,13 +1,12 @@
 """GPU parity at the library's size limits and across wavefront layouts.
 
-* Maximum model sizes against the oracle: 8 request types for WAIT and FCFS,
-  16 types and 16 segments for Nested WAIT, 255 histogram edges.
-* Launches large enough that the host packs 16 or 32 replicas per wavefront
-  (known-length kernels with up to 4 types stop at 32 and add wavefronts;
-  64 per wavefront is covered with 8 types in test_gpu_max_sizes.py): a
-  replica's outputs depend only on (model, policy, seed, replica id,
-  horizon), so the same replicas run alone (8 per wavefront) must give
-  bit-identical results.
+* Many request types against the oracle: 8, 16 and up to 64 types for WAIT and
+  FCFS, 16 types and 16 segments and up to 40 types for Nested WAIT, 255
+  histogram edges.
+* Launches whose wavefronts are full (16 replicas of three types; other widths
+  of a lane group in test_gpu_max_sizes.py): a replica's outputs depend only on
+  (model, policy, seed, replica id, horizon), so the same replicas run alone
+  (spread over more wavefronts) must give bit-identical results.
 """
 import numpy as np
 import pytest
@@ -71,14 +70,14 @@ def _subset_equal(B, jobs, horizon, picks, ctx):
     print(f"[gpu] {ctx}: {len(idx)} replicas identical to a separate launch", flush=True)
 
 
-@pytest.mark.parametrize("reps", [512, 1024, 2048])   # 16, 32, 32 (2,048 wavefronts)
+@pytest.mark.parametrize("reps", [512, 1024, 2048])   # 1,024 to 4,096 wavefronts of 16
 def test_wait_layouts_agree(B, reps):
     jobs = W.config2(replicas=reps)
     _subset_equal(B, jobs, 400, [(0, 0, 33), (17, reps - 40, reps), (31, 5, 9)],
                   f"WAIT, {32 * reps} replicas")
 
 
-@pytest.mark.parametrize("reps", [512, 1024])         # 16, 32 per wavefront
+@pytest.mark.parametrize("reps", [512, 1024])         # 1,024 and 2,048 wavefronts of 16
 def test_nested_layouts_agree(B, reps):
     jobs = W.config3(replicas=reps)
     _subset_equal(B, jobs, 300, [(0, 0, 33), (20, reps - 40, reps)],
@@ -87,8 +86,7 @@ def test_nested_layouts_agree(B, reps):
 
 def test_sixteen_types_wait_and_fcfs(B):
     """16 request types under WAIT and FCFS (thresholds up to 3, 255 edges),
-    37 + 29 replicas: the 16-slot known-length kernel at 32 replicas per
-    wavefront, against the oracle."""
+    37 + 29 replicas, in lane groups of 16, against the oracle."""
     rng = np.random.default_rng(16)
     l, lam = _types(rng, 16)
     lp = [int(x) for x in rng.integers(1, 64, 16)]
@@ -138,7 +136,7 @@ def test_many_types_nested_and_fcfs(B):
 
 
 def test_many_types_wait(B):
-    """WAIT beyond 16 types (per-type state in LDS columns): 20 and 64 types,
+    """WAIT beyond 16 types (lane groups of 32 and 64): 20 and 64 types,
     thresholds up to 3, tight memory; WAIT-no-wait with 24 types; per-stage
     caps on 20 types; an arrival list with 40 types; against the oracle."""
     rng = np.random.default_rng(65)

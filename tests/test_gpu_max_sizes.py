@@ -1,9 +1,9 @@
-"""The widest instantiations at the library's size limits, in launches large
-enough that the host packs the most replicas per wavefront: Nested WAIT with
-16 types, 16 segments and 255 histogram edges at 32 replicas per wavefront
-(65,536 replicas), with and without a 32-point rate profile; WAIT and FCFS
-with 8 types at 64 replicas per wavefront.  Sampled replicas (first, last
-and interior wavefronts) are compared with the oracle field by field."""
+"""Launches large enough that every wavefront is full (a lane group of 1 to 64
+lanes per replica: 64 replicas to a wavefront down to one), at the library's
+size limits: Nested WAIT with 16 types, 16 segments and 255 histogram edges
+(65,536 replicas), with and without a 32-point rate profile; WAIT and FCFS with
+8 types; every width of a lane group.  Sampled replicas (first, last and
+interior wavefronts) are compared with the oracle field by field."""
 import numpy as np
 import pytest
 
@@ -44,11 +44,11 @@ def _nested16(rng):
                       record_capacity=1 << 9)
 
 
-def test_nested_16x16_at_32_per_wavefront():
+def test_nested_16x16():
     B = sim_module()
     wl = _nested16(np.random.default_rng(1616))
     print(f"[gpu] nested 16x16, {R} replicas", flush=True)
-    g = _sampled(B, [W.Job(wl, 7, W.ids(R))], 400, "nested 16 types x 16 segments, 32/wave")
+    g = _sampled(B, [W.Job(wl, 7, W.ids(R))], 400, "nested 16 types x 16 segments")
     assert g["arrivals"].min() >= 0 and g["completions"].sum() > 0
 
 
@@ -61,7 +61,7 @@ def test_nested_16x16_with_profile():
     _sampled(B, [W.Job(wl, 8, W.ids(R))], 400, "nested 16x16, 32-point profile")
 
 
-def test_wait_and_fcfs_8_types_at_64_per_wavefront():
+def test_wait_and_fcfs_8_types():
     B = sim_module()
     rng = np.random.default_rng(88)
     l = [int(x) for x in rng.integers(4, 200, 8)]
@@ -76,7 +76,7 @@ def test_wait_and_fcfs_8_types_at_64_per_wavefront():
                       out_len=lp, reserve=0.01, hist_edges=edges, record_capacity=1 << 10)
     print(f"[gpu] 8 types, WAIT and FCFS, {R} replicas each", flush=True)
     _sampled(B, [W.Job(wait, 3, W.ids(R)), W.Job(fcfs, 4, W.ids(R))], 600,
-             "WAIT and FCFS, 8 types, 64/wave")
+             "WAIT and FCFS, 8 types")
 
 
 @pytest.mark.parametrize("cap", [65535, 70000])
@@ -95,3 +95,33 @@ def test_nested_long_output_rows(cap):
                     hist_edges=W.default_edges(5.0, 40), record_capacity=1 << 12)
     check(B, [W.Job(wl, int(rng.integers(0, 2**63)), W.ids(9))], 600,
           f"nested, output rows of {cap - 1} entries")
+
+
+@pytest.mark.parametrize("m", [1, 2, 3, 5, 11, 17, 40])
+def test_full_wavefronts(m):
+    """Every lane-group width (1, 2, 4, 8, 16, 32 and 64) with as many replicas
+    as fill its wavefronts, the last one in part: WAIT with cohorts, FCFS, Nested
+    WAIT with unit thresholds; and an arrival list, whose wavefronts hold the most
+    replicas (64 of one type)."""
+    B = sim_module()
+    rng = np.random.default_rng(700 + m)
+    n = 33001
+    picks = (0, 1, 62, 63, 64, 16500, n - 34, n - 2, n - 1)
+    l = [int(x) for x in rng.integers(4, 60, m)]
+    lp = [int(x) for x in rng.integers(1, 20, m)]
+    kw = dict(d0=2.0, d1=0.005, C=6 * max(a + b for a, b in zip(l, lp)),
+              hist_edges=W.default_edges(2.0, 64), record_capacity=1 << 8)
+    lam = [float(x) / m for x in rng.uniform(0.1, 0.6, m)]
+    wls = [W.Workload(prompt_len=l, lam=lam, policy="wait",
+                      n=[int(x) for x in rng.integers(1, 4, m)], out_len=lp, **kw)]
+    if m <= 16:
+        wls.append(W.Workload(prompt_len=l, lam=lam, policy="fcfs", n=[], out_len=lp, **kw))
+    cdf = np.stack([W.geometric_cdf_table(float(rng.uniform(2.0, 20.0)), 30) for _ in range(m)])
+    wls.append(W.Workload(prompt_len=l, lam=lam, policy="nested", n=[1] * 3, out_cap=30, out_cdf=cdf,
+                          seg_end=[4, 11, 30], **kw))
+    g = _sampled(B, [W.Job(wl, 5, W.ids(n)) for wl in wls], 150, f"{m} types, full wavefronts", picks)
+    assert g["evictions"].sum() > 0
+    times = np.sort(rng.uniform(0.0, 300.0, 200))
+    wl = W.trace_workload("wait", l, lp, 2.0, 0.005, kw["C"], [2] * m, times, rng.integers(0, m, 200),
+                          record_capacity=1 << 8)
+    _sampled(B, [W.Job(wl, 0, W.ids(n))], 150, f"{m} types, list, full wavefronts", picks)

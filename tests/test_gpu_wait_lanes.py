@@ -76,13 +76,15 @@ def test_gaps_below_the_clock():
 
 
 def test_more_replicas_than_a_launch_spreads():
-    """32 jobs of 512 and of 37 replicas: wavefronts full of groups, and the
-    narrow ones of a small launch, give the same replicas the same bits."""
+    """32 jobs of 1,200 and of 37 replicas: wavefronts full of groups, and the
+    narrow ones of a small launch (against the oracle), give the same replicas
+    the same bits."""
     B = sim_module()
     rng = np.random.default_rng(12)
     base = [_job(rng, 3, 1, 4, "wait", 1) for _ in range(32)]
     wide = B.run_batch([dataclasses.replace(j, replica_ids=W.ids(1200)) for j in base], 200)
-    thin = B.run_batch([dataclasses.replace(j, replica_ids=W.ids(37)) for j in base], 200)
+    thin, _ = check(B, [dataclasses.replace(j, replica_ids=W.ids(37)) for j in base], 200,
+                    "32 x 37 replicas, three types")
     idx = np.concatenate([1200 * k + np.arange(37) for k in range(32)])
     for k in wide:
         assert np.array_equal(wide[k][idx], thin[k]), k
