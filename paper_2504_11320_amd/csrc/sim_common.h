@@ -95,7 +95,7 @@ struct KArgs {
   int32_t resume;
   int32_t any_trace;   // some job of this launch replays a fixed arrival list
   int32_t any_tv;      // some job of this launch has time-varying rates
-  int32_t lanes;       // replicas per wavefront (lanes >= this are padding)
+  int32_t lanes;       // replicas per row of 64 list entries (the rest are padding)
   int32_t unit_n;      // WAIT or Nested WAIT launch whose thresholds are all 1
   int32_t any_caps;    // some job of this launch has per-stage caps
   int32_t nr;          // WAIT, FCFS: replicas per wavefront (a divisor of `lanes`)

@@ -19,10 +19,9 @@
 // and in a longer queue the next records are loaded at a launch and land at
 // the batch's completion step, so the scan seldom waits for memory.
 //
-// Arithmetic follows the model contract exactly (same IEEE operations, no FMA
-// contraction): arrivals add their area terms in time order; a batch's
-// completions add their latencies per type in admission order, then the types
-// in turn.
+// Arithmetic is the model's (the same IEEE operations, no FMA contraction), in
+// its order but for one sum: a batch's completions sum their latencies per type
+// in admission order, then the types in turn (the model adds them one by one).
 //
 // What bounds it: a wavefront's latency per batch (a replica is a serial chain
 // of events).  32 rates x 1024 replicas of the Llama-shaped mix with 512-token

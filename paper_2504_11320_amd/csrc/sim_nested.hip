@@ -1,5 +1,5 @@
 // sim_nested.hip -- instantiates the Nested WAIT simulation kernel (Algorithm
-// 2) for launches with constant arrival rates.
+// 2) for constant arrival rates and arrival lists, and picks a launch's kernel.
 #include "sim_nested_impl.h"
 
 namespace wsim {

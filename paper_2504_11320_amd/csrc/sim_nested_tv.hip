@@ -1,5 +1,6 @@
 // sim_nested_tv.hip -- instantiates the Nested WAIT simulation kernel
-// (Algorithm 2) for launches with time-varying arrival rates.
+// (Algorithm 2) for launches with time-varying arrival rates, per-stage caps or
+// a per-batch trace.
 #include "sim_nested_impl.h"
 
 namespace wsim {

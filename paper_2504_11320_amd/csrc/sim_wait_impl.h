@@ -25,10 +25,10 @@
 // pop at the front, LIFO evictions pop at the back, and a step costs
 // O(events), not O(stages).
 //
-// Arithmetic follows the model contract exactly (same IEEE operations, no FMA
-// contraction): a batch's arrivals and its completions sum their area terms
-// and latencies per type, in time and in admission order, then the types in
-// turn.
+// Arithmetic is the model's (the same IEEE operations, no FMA contraction), in
+// its order but for three sums: a batch's arrivals and its completions sum their
+// area terms and latencies per type, in time and in admission order, then the
+// types in turn (the model adds them one by one).
 //
 // What bounds it: a replica is a serial chain of events, so a wavefront's
 // latency per batch.  Per wavefront and batch of the Llama-shaped unit

@@ -293,7 +293,7 @@ struct Layout {
   JobHost *jobs = nullptr;     // [n_jobs]: `own`, or storage of the caller
   std::vector<JobHost> own;
   int32_t list_count[kKinds] = {0, 0, 0, 0};
-  int32_t lanes[kKinds] = {64, 64, 64, 64};  // replicas per wavefront, per launch
+  int32_t lanes[kKinds] = {64, 64, 64, 64};  // replicas per row of the launch's list
   uint64_t list_off[kKinds] = {0, 0, 0, 0};
   int32_t max_m[kKinds] = {0, 0, 0, 0};
   int32_t max_seg = 0;
