@@ -214,7 +214,7 @@ sim_fcfs_kernel(KArgs A) {
   }
   ListArrivals<G> lst(s_arr.at, s_arr.ak, (const double *)(A.ws + J.off_tr_time),
                       (const int32_t *)(A.ws + J.off_tr_type), J.n_trace, tridx);
-  if (LIST && trace) lst.start(live);
+  if (trace) lst.start(live);
 
   // ---- the queue ----------------------------------------------------------
   // Records qh .. qc-1 are in LDS (a power of two of them at most, shared out
@@ -304,13 +304,15 @@ sim_fcfs_kernel(KArgs A) {
     more &= ~(go & full);
     if ((me & low) != 0) arr.refill(live, me);
     push_q(go, me, ta);
-    if (LIST && trace) {
-      if (in(me)) arr.rp++;
-      lst.advance(go, live);
-    } else if (in(me)) {
-      arr.advance();
-      if (arr.limited()) flags |= kFlagThin;
+    if (in(me)) {
+      if (trace) {
+        arr.rp++;
+      } else {
+        arr.advance();
+        if (arr.limited()) flags |= kFlagThin;
+      }
     }
+    if (trace) lst.advance(go, live);
   };
 
   // Push a prompt admitted in this batch, at position p, at the back of this
@@ -463,7 +465,7 @@ sim_fcfs_kernel(KArgs A) {
 
     // ---- arrivals during the batch ----------------------------------------
     Mask inb = live;
-    if (LIST && trace) {
+    if (trace) {
       for (;;) {
         const Mask go = ballot(lst.tn <= t_end) & inb;
         if (go == 0) break;

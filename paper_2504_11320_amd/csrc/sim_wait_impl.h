@@ -226,7 +226,7 @@ sim_wait_kernel(KArgs A) {
   }
   ListArrivals<G> lst(s_arr.at, s_arr.ak, (const double *)(A.ws + J.off_tr_time),
                       (const int32_t *)(A.ws + J.off_tr_type), J.n_trace, tridx);
-  if (LIST && trace) lst.start(live);
+  if (trace) lst.start(live);
 
   // ---- arrivals ---------------------------------------------------------------
   // The group's next arrival and the lanes of its type(s).
@@ -261,14 +261,14 @@ sim_wait_kernel(KArgs A) {
     if (in(me)) {
       qr[qt & qmask] = ta;  // a full queue is not read again
       qt++;
+      if (trace) {
+        arr.rp++;
+      } else {
+        arr.advance();
+        if (arr.limited()) flags |= kFlagThin;
+      }
     }
-    if (LIST && trace) {
-      if (in(me)) arr.rp++;
-      lst.advance(go, live);
-    } else if (in(me)) {
-      arr.advance();
-      if (arr.limited()) flags |= kFlagThin;
-    }
+    if (trace) lst.advance(go, live);
     return me;
   };
 
@@ -447,7 +447,7 @@ sim_wait_kernel(KArgs A) {
         part_a += in(me) ? t_end - ta : 0.0;
       }
     };
-    if (LIST && trace) {  // the list's next arrival, whichever its type
+    if (trace) {  // the list's next arrival, whichever its type
       for (;;) {
         const Mask go = ballot(lst.tn <= t_end) & inb;
         if (go == 0) break;
