@@ -168,10 +168,12 @@ sim_nested_unit_kernel(KArgs A) {
     peak = Mres = pendft = 0;
     qh = qt = 0;
     if (valid) {
-      // calendar buckets start empty: each segment's by the whole group
+      // calendar buckets start empty: each segment's by the whole group (its size
+      // is read before: after a store it would be loaded again)
       for (int kk = 0; kk < L; ++kk) {
         uint32_t *b = (uint32_t *)(blk + J.off_bkt[kk]);
-        for (int x = gl; x < J.seg_delta[kk]; x += G) b[x] = kNil;
+        const int n = J.seg_delta[kk];
+        for (int x = gl; x < n; x += G) b[x] = kNil;
       }
       for (int b = gl; b < A.hist_stride; b += G) hist[b] = 0;  // whole row, padding included
     }
