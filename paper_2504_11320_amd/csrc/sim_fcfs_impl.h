@@ -52,9 +52,10 @@ sim_fcfs_kernel(KArgs A) {
   constexpr int RING = 512;   // arrival times drawn ahead, of a wavefront
   constexpr int QRING = 256;  // queue records in LDS, of a wavefront
   constexpr int NL = G >= 4 ? 1 : 4 / G;  // queue records a lane loads at a time
-  // the last records pushed on each deque, for LIFO evictions (with lists as
-  // many as leave room for two wavefronts per SIMD with 3 to 8 types)
-  constexpr int WB = LIST ? 4 : 8;
+  // the last records pushed on each deque, for LIFO evictions (in the general
+  // instantiations as many as leave room for two wavefronts per SIMD with up to
+  // 8 types)
+  constexpr int WB = TV ? 4 : 8;
   constexpr int KC = 8;  // records at the front of the deque loaded at the launch
   __shared__ typename Arrivals<G, TV, RING>::Lds s_arr;
   __shared__ DRec s_win[WB][64];
