@@ -51,6 +51,17 @@ def test_full_queues():
     assert (g["flags"] & B.WS_FLAG_CAPACITY).sum() > 0
 
 
+def test_queue_full_at_the_launch():
+    """Evictions of the repair before a launch that overflow the queue: the
+    batch runs, but takes no arrival any more."""
+    B = sim_module()
+    rng = np.random.default_rng(17)
+    jobs = [_job(rng, m, ENDS[e], 24, room, 4.0, 16) for m in (3, 8) for e in (4, 8, 16)
+            for room in (1.0, 1.3)]
+    g, _ = check(B, jobs, 200, "unit Nested WAIT, queue full at the launch")
+    assert (g["flags"] & B.WS_FLAG_CAPACITY).all()
+
+
 def test_between_kernels():
     """Parts of a run on the unit kernel and on the general one (a traced
     advance), in both orders, end where one advance ends."""
