@@ -552,7 +552,6 @@ sim_nested_unit_kernel(KArgs A) {
     qh += in(group_spread<G>(first)) ? 1u : 0u;
 
     // ---- pre-launch repair on the projected state ----------------------------
-    Mask inb = live;  // groups that take this batch's arrivals
     {
       Mask over = ballot(mplus > C) & live;
       if (over != 0) {
@@ -562,8 +561,9 @@ sim_nested_unit_kernel(KArgs A) {
           over &= ballot(mplus > C);
         } while (over != 0);
         if (in(all) && mplus > C) flags |= kFlagOverflow;
-        // a queue that an evicted prompt overflowed takes no more of them
-        inb &= ~ballot((flags & kFlagCap) != 0);
+        // a replica whose queue an evicted prompt overflowed takes no arrival any
+        // more (it ends at its next decision)
+        if ((flags & kFlagCap) != 0) arr.tn = INFINITY;
       }
     }
     // The walk's first record is there: the one after it is loaded now.
@@ -587,6 +587,7 @@ sim_nested_unit_kernel(KArgs A) {
     const double t_end = t + tau;
 
     // ---- arrivals during the batch -----------------------------------------
+    Mask inb = live;
     for (;;) {
       const double ta = group_min<G>(arr.tn);
       const Mask go = ballot(ta <= t_end) & inb;
