@@ -25,9 +25,9 @@
 //
 // What bounds it: a wavefront's latency per batch (a replica is a serial chain
 // of events).  32 rates x 1024 replicas of the Llama-shaped mix with 512-token
-// chunks: 160 vector and 77 scalar instructions per wavefront and batch, 11.4
-// ms per 5,000 batches (18.1 with one lane per replica and per-type register
-// arrays); half of the waves' cycles are waits.  2 x 9,216 replicas of one
+// chunks: 158 vector, 77 scalar and 35 branch instructions per wavefront and
+// batch, 11.4 ms per 5,000 batches (18.1 with one lane per replica and per-type
+// register arrays); half of the waves' cycles are waits.  2 x 9,216 replicas of one
 // type, 6.5 arrivals a batch, beside the same under WAIT: 13.2 against 29.4 ms
 // per 1,000 batches (records were loaded one by one as they were popped).
 #pragma once

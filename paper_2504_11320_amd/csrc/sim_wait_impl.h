@@ -33,12 +33,12 @@
 // What bounds it: a replica is a serial chain of events, so a wavefront's
 // latency per batch.  Per wavefront and batch of the Llama-shaped unit
 // threshold sweep (32,768 replicas, 16 to a wavefront, two wavefronts per
-// SIMD) it issues 370 vector and 145 scalar instructions, where one lane per
-// replica with per-type register arrays issued 1,190 and 440 (select chains,
-// one body per type): 14.4 against 24.2 ms per 5,000 batches.  Half of a
-// batch is waits, so every record of a batch is loaded at its launch and
-// waited for once, at its completion step, before the histogram's updates: a
-// wait after them would wait for them too (17.4 ms).
+// SIMD) it issues 384 vector, 119 scalar and 49 branch instructions (the SIMDs
+// issue 70 % of the time); one lane per replica with per-type register arrays
+// (select chains, one body per type) took 24.2 ms per 5,000 batches, this 14.2.
+// 56 % of a wavefront's cycles are waits, so every record of a batch is loaded
+// at its launch and waited for once, at its completion step, before the
+// histogram's updates: a wait after them would wait for them too (17.4 ms).
 #pragma once
 
 #include "sim_arrivals.h"
