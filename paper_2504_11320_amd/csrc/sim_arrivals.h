@@ -164,15 +164,15 @@ struct Arrivals {
   }
   // The pending arrivals of the lanes of `live`, after the first refill.  With a
   // rate profile a lane thins its draws one after another, and a call may end
-  // after a few batches, so that refill draws 16 at most (and never more than
-  // half of a ring): 20 calls of one batch, 4 replicas of one type, took 0.75 ms
-  // with 32 and take 0.59 (0.58 with 4); 512 replicas 0.84 and 0.68 (0.91 with 4,
-  // which the batch uses up).
-  __device__ __forceinline__ void start(Mask live) {
+  // after a few batches, so that refill draws `first` at most (and never more than
+  // half of a ring): 20 calls of one batch, WAIT, 4 replicas of one type, took 0.75
+  // ms with 32 and take 0.59 with 16 (0.58 with 4); 512 replicas 0.84 and 0.68
+  // (0.91 with 4, which the batch uses up).
+  __device__ __forceinline__ void start(Mask live, uint32_t first = 16u) {
     wave_lds_sync();
     if constexpr (TV) {
       const uint32_t half = gu;
-      if (tv) gu = min(half, 16u);
+      if (tv) gu = min(half, first);
       gu_log2 = __builtin_ctz(gu);
       refill(live, live, 1u);
       gu = half;
